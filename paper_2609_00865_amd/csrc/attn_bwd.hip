@@ -60,6 +60,7 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_kernel(BwdArgs a) {
   __shared__ __align__(1024) u16 sKbuf[2 * BK * D];
   __shared__ __align__(1024) u16 sVbuf[2 * BK * D];
   __shared__ __align__(16) int sOmbuf[2 * BK];
+  __shared__ __align__(16) uint32_t sVis[IV ? 4 : 1][BK];   // per wave: a key's rows, as bits
 
   int xcd, local;
   xcd_split(xcd, local);
@@ -153,8 +154,14 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_kernel(BwdArgs a) {
     const int* sOm = sOmbuf + buf * BK;
     const int j0 = kt * BK;
     // only a partial tile holding a key with several live intervals (masks
-    // with restoring edits) walks the interval lists
+    // with restoring edits) walks the interval lists: once per key, as the
+    // bits of this wave's 32 rows
     const bool tile_iv = IV && !full && __any(sOm[lane] < 0);
+    if (tile_iv) {
+      sVis[wave][lane] = mv_key_row_bits(j0 + lane, sOm[lane], qt * BQ + wave * 32, a.mask.iv_ptr,
+                                         a.mask.iv);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
 
     // The tile's MFMAs in one fixed sequence: S^T and dP^T of key half 0,
     // of half 1, then dQ^T += K^T dS^T of both halves.  The vector work of
@@ -185,13 +192,12 @@ __global__ __launch_bounds__(256, 2) void bwd_dq_kernel(BwdArgs a) {
       if (tile_iv) {
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
-          const int4 om = *reinterpret_cast<const int4*>(&sOm[kb * 32 + q4 * 8 + g * 4]);
-          const int omv[4] = {om.x, om.y, om.z, om.w};
+          const uint4 w = *reinterpret_cast<const uint4*>(&sVis[wave][kb * 32 + q4 * 8 + g * 4]);
+          const uint32_t wv[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
             const int r = q4 * 4 + u;
-            const int key = j0 + kb * 32 + q4 * 8 + g * 4 + u;
-            s[kb][r] = mv_visible_iv(qrow, key, omv[u], a.mask.iv_ptr, a.mask.iv) ? s[kb][r] : 0.f;
+            s[kb][r] = (wv[u] >> c) & 1u ? s[kb][r] : 0.f;
           }
         }
       } else {   // per element a select, not a branch
@@ -488,6 +494,25 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(BwdArgs a) {
     }
   }
   __syncthreads();   // block 0 landed
+  // Masks with restoring edits: the first NIV further live intervals of the
+  // lane's key in registers (empty ones past the list's end), the rest, if
+  // any lane has them, re-read for every unit.
+  constexpr int NIV = 3;
+  int ivb[NIV], ive[NIV], iv_rest = 0, iv_end = 0;
+  bool iv_more = false;
+  if (IV) {
+    const bool has = iv_tile && om < 0;
+    const int p = has ? a.mask.iv_ptr[key] : 0;
+    iv_end = has ? a.mask.iv_ptr[key + 1] : 0;
+#pragma unroll
+    for (int q = 0; q < NIV; ++q) {
+      const bool in = p + q < iv_end;
+      ivb[q] = in ? a.mask.iv[2 * (p + q)] : 0;
+      ive[q] = in ? a.mask.iv[2 * (p + q) + 1] : 0;
+    }
+    iv_rest = p + NIV;
+    iv_more = __any(iv_rest < iv_end);   // wave-uniform
+  }
   // unit v = 6 i + VM (computed in the interval before the accumulating
   // wave takes it): buffer VM / 2, rows and operand half constant
   auto unit = [&](auto vm_tag, int v) {
@@ -522,6 +547,20 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(BwdArgs a) {
     const float* sD = sDbuf + buf * BQ;   // -D
     const int i0 = (qb0 + st % nqb) * BQ;
     const bool full = (i0 >= j1 - 1) && (i0 + BQ <= om_min);   // block-uniform
+    // Key tiles with several live intervals: the unit's 32 rows that see this
+    // lane's key, as bits, once per unit (a walk of the list per score
+    // element took 878 us on 2903 tokens, 8 / 2 heads of 64)
+    uint32_t vis = 0;
+    if (IV && iv_tile && !full) {
+      const int r0 = i0 + mb * 32;
+      vis = mv_row_bits(key, mv_first_end(om), r0);
+#pragma unroll
+      for (int q = 0; q < NIV; ++q) vis |= mv_row_bits(ivb[q], ive[q], r0);
+      if (iv_more)
+        for (int q = iv_rest; q < iv_end; ++q)
+          vis |= mv_row_bits(a.mask.iv[2 * q], a.mask.iv[2 * q + 1], r0);
+      vis >>= g * 4;   // this lane's rows: bits q4 * 8 + e
+    }
 #pragma unroll
     for (int q4 = 0; q4 < 4; ++q4) {
       const int qo = mb * 32 + q4 * 8 + g * 4;
@@ -537,9 +576,9 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(BwdArgs a) {
           const int i = i0 + qo + e;
           // single-interval keys: row i sees this lane's key iff 0 <= i -
           // key < om - key
-          const bool vis = (IV && iv_tile) ? mv_visible_iv(i, key, om, a.mask.iv_ptr, a.mask.iv)
+          const bool see = (IV && iv_tile) ? (vis >> (q4 * 8 + e)) & 1u
                                            : uint32_t(i - key) < uint32_t(om - key);
-          s[q4 * 4 + e] = vis ? s[q4 * 4 + e] : 0.f;
+          s[q4 * 4 + e] = see ? s[q4 * 4 + e] : 0.f;
         }
       }
 #pragma unroll

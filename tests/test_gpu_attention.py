@@ -144,6 +144,22 @@ def test_scores_far_above_earlier_tiles(jump, d):
                 f"growing scores (jump={jump}, d={d})")
 
 
+@pytest.mark.parametrize("d", [128, 64])
+def test_keys_with_many_intervals(d):
+    """Tokens that leave and come back seven times: more live intervals than
+    the dK/dV pass keeps in registers."""
+    edits, on = [], True
+    for i, J in enumerate(range(100, 660, 40)):
+        span = ((20, 61),)
+        edits.append(synth.Edit(J, span, (J, J)) if on else synth.Edit(J, (), (J, J), span))
+        on = not on
+    trajs = [synth.Trajectory(0, 700, tuple(edits))]
+    gen = torch.Generator().manual_seed(61)
+    q, do = (torch.randn(700, 4, d, generator=gen).to(torch.bfloat16) for _ in range(2))
+    k, v = (torch.randn(700, 2, d, generator=gen).to(torch.bfloat16) for _ in range(2))
+    _check_full(trajs, q, k, v, do, f"seven intervals/d{d}")
+
+
 def test_no_compression_is_causal():
     T, hq, hkv, d = 700, 4, 1, 128
     gen = torch.Generator().manual_seed(11)
