@@ -298,6 +298,8 @@ void build_bwd_schedule(mv_view_mask& m) {
   m.bwd_tiles.assign(4 * size_t(m.n_kt128), 0);
   m.bwd_items.clear();
   m.bwd_red.clear();
+  m.bwd_cum.assign(1, 0);
+  m.bwd_cost.assign(1, 0);
   int32_t slot = 0;
   std::vector<std::array<int32_t, 4>> items;
   for (int32_t kt = 0; kt < m.n_kt128; ++kt) {
@@ -310,6 +312,11 @@ void build_bwd_schedule(mv_view_mask& m) {
     // rows seeing some key of the tile form the contiguous range [j0, hi)
     const int32_t qb0 = j0 / BQ, qb1 = (hi + BQ - 1) / BQ;
     const int32_t n = qb1 - qb0, chunks = (n + CH - 1) / CH;
+    m.bwd_cum.push_back(m.bwd_cum.back() + n);
+    // blocks the kernel takes without a mask: rows from the tile's last key
+    // on, up to the first row some key is not live at
+    const int32_t f0 = (j1 - 1 + BQ - 1) / BQ, f1 = std::min(qb1, lo / BQ);
+    m.bwd_cost.push_back(m.bwd_cost.back() + 8 * int64_t(n) + (n - std::max(0, f1 - f0)));
     m.bwd_tiles[4 * kt + 0] = lo;
     m.bwd_tiles[4 * kt + 1] = hi;
     if (chunks == 1) {
@@ -359,7 +366,11 @@ void build_bwd_schedule(mv_view_mask& m) {
     items[p] = order[q];
   }
   int64_t bwd_pairs = 0;
-  for (const auto& it : items) bwd_pairs += int64_t(it[2] - it[1]) * BQ * BK;
+  m.bwd_max_blocks = 0;
+  for (const auto& it : items) {
+    bwd_pairs += int64_t(it[2] - it[1]) * BQ * BK;
+    m.bwd_max_blocks = std::max(m.bwd_max_blocks, it[2] - it[1]);
+  }
   m.stats.bwd_tile_pairs = bwd_pairs;
   m.bwd_items.reserve(items.size() * 4);
   for (const auto& it : items) m.bwd_items.insert(m.bwd_items.end(), it.begin(), it.end());
@@ -369,11 +380,11 @@ void build_bwd_schedule(mv_view_mask& m) {
 }
 
 void layout_device(mv_view_mask& m) {
-  const std::vector<int32_t>* arrs[10] = {&m.omega,     &m.kt_minmax, &m.q_ptr,    &m.k_list,
+  const std::vector<int32_t>* arrs[11] = {&m.omega,     &m.kt_minmax, &m.q_ptr,    &m.k_list,
                                           &m.qt_order,  &m.bwd_items, &m.bwd_tiles, &m.bwd_red,
-                                          &m.iv_ptr,    &m.iv};
+                                          &m.iv_ptr,    &m.iv,        &m.bwd_cum};
   size_t off = 0;
-  for (int i = 0; i < 10; ++i) {
+  for (int i = 0; i < 11; ++i) {
     m.off[i] = off;
     off = align256(off + std::max<size_t>(1, arrs[i]->size()) * sizeof(int32_t));
   }
@@ -474,12 +485,12 @@ mv_status mv_view_mask_upload(mv_view_mask* m, void* dev_buf, size_t bytes, hipS
     os << "mask buffer has " << bytes << " bytes, needs " << m->bytes;
     return bad(MV_ERR_WORKSPACE, os.str());
   }
-  const std::vector<int32_t>* arrs[10] = {&m->omega,     &m->kt_minmax, &m->q_ptr,
+  const std::vector<int32_t>* arrs[11] = {&m->omega,     &m->kt_minmax, &m->q_ptr,
                                           &m->k_list,    &m->qt_order,  &m->bwd_items,
                                           &m->bwd_tiles, &m->bwd_red,   &m->iv_ptr,
-                                          &m->iv};
+                                          &m->iv,        &m->bwd_cum};
   char* base = static_cast<char*>(dev_buf);
-  for (int i = 0; i < 10; ++i) {
+  for (int i = 0; i < 11; ++i) {
     if (arrs[i]->empty()) continue;
     hipError_t e = hipMemcpyAsync(base + m->off[i], arrs[i]->data(),
                                   arrs[i]->size() * sizeof(int32_t), hipMemcpyHostToDevice, stream);
@@ -490,7 +501,7 @@ mv_status mv_view_mask_upload(mv_view_mask* m, void* dev_buf, size_t bytes, hipS
   m->dev = dev_buf;
   m->device = dev;
   auto at = [&](int i) { return reinterpret_cast<const int32_t*>(base + m->off[i]); };
-  m->d = mv_mask_dev{at(0), at(1), at(2), at(3), at(4), at(5), at(6), at(7), at(8), at(9)};
+  m->d = mv_mask_dev{at(0), at(1), at(2), at(3), at(4), at(5), at(6), at(7), at(8), at(9), at(10)};
   return MV_OK;
 }
 

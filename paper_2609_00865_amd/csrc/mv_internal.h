@@ -23,6 +23,7 @@ constexpr int kBwdBlockQ = 64;
 constexpr int kBwdChunk = 32;
 // Blocks are dealt to the 8 XCDs round-robin by the dispatcher.
 constexpr int kNumXcd = 8;
+constexpr int kNumCu = 256;
 
 void set_error(const std::string& msg);
 
@@ -55,20 +56,25 @@ struct mv_mask_dev {
   const int32_t* bwd_red;    // [n_red] key tiles whose partials are reduced
   const int32_t* iv_ptr;     // [T + 1] per-key ranges of further live intervals
   const int32_t* iv;         // [2 * n_iv] (begin, end) of those intervals
+  const int32_t* bwd_cum;    // [n_kt128 + 1] 64-row query blocks of the key tiles before
 };
 
 struct mv_view_mask {
   int32_t T = 0;
   int32_t n_qt = 0, n_kt64 = 0, n_kt128 = 0;
   std::vector<int32_t> omega, kt_minmax, q_ptr, k_list, qt_order;
-  std::vector<int32_t> bwd_items, bwd_tiles, bwd_red;
+  std::vector<int32_t> bwd_items, bwd_tiles, bwd_red, bwd_cum;
+  // cost of the dK/dV steps of the key tiles before, per query head: 8 a
+  // 64-row block, 1 more if the block needs the mask (host only)
+  std::vector<int64_t> bwd_cost;
+  int32_t bwd_max_blocks = 0;       // 64-row blocks of the longest dK/dV work item
   std::vector<int32_t> iv_ptr, iv;  // further live intervals of restored keys
   int32_t n_slots = 0;
   int32_t kind = MV_VIEW_LIVE;
   std::vector<int32_t> leaf_token, leaf_teacher, leaf_student;  // diverging leaves
   mv_mask_stats stats{};
   // device copy
-  size_t off[10] = {0};
+  size_t off[11] = {0};
   size_t bytes = 0;
   void* dev = nullptr;
   int device = -1;

@@ -144,6 +144,25 @@ def test_scores_far_above_earlier_tiles(jump, d):
                 f"growing scores (jump={jump}, d={d})")
 
 
+@pytest.mark.parametrize("d,hq,hkv,lens,restore,seed", [
+    (128, 8, 2, [1100, 333], 0, 51),     # fewer workers than CUs
+    (64, 14, 2, [1537], 30, 52),         # group of 7, interval lists
+    (128, 4, 4, [2600, 129, 700], 0, 53),   # no grouping, short last tile
+    (64, 12, 12, [1301, 64], 0, 54),
+])
+def test_backward_in_equal_shares(d, hq, hkv, lens, restore, seed):
+    """Sizes whose dK/dV pass is cut into equal shares per CU: shares that
+    start and end inside key tiles, span several tiles and cross KV heads."""
+    rng = np.random.default_rng(seed)
+    trajs = synth.random_trajectories(rng, lens, max_edits=6, max_span=200, summary_max=30,
+                                      restore_max=restore)
+    T = trajs[-1].end
+    gen = torch.Generator().manual_seed(seed)
+    q, do = (torch.randn(T, hq, d, generator=gen).to(torch.bfloat16) for _ in range(2))
+    k, v = (torch.randn(T, hkv, d, generator=gen).to(torch.bfloat16) for _ in range(2))
+    _check_full(trajs, q, k, v, do, f"shares{lens}/d{d}/{hq}:{hkv}")
+
+
 @pytest.mark.parametrize("d", [128, 64])
 def test_keys_with_many_intervals(d):
     """Tokens that leave and come back seven times: more live intervals than
