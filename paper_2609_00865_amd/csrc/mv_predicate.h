@@ -47,18 +47,20 @@ MV_HD bool mv_visible_k(int i, int j, int omega_j, const int* iv_ptr, const int*
 }
 
 #if defined(__HIPCC__)
-// The visibility bits of one lane's 32 score elements of a 64-key tile whose
-// keys may have several live intervals, in the attention kernels' layout:
-// element e (bit e) is key j0 + (e / 16) * 32 + ((e % 16) / 4) * 8 + g * 4 +
-// e % 4 for query row i; omega of the tile's key k at om[k].  Out of line: the
-// interval walk stays off the register budget of the kernels' pipelined
-// loops, which call it only for tiles that hold such a key.
-[[maybe_unused]] static __device__ __noinline__ uint32_t
-mv_visible_iv_bits(int i, int j0, int g, const int* om, const int* iv_ptr, const int* iv) {
-  uint32_t bits = 0;
-  for (int e = 0; e < 32; ++e) {
-    const int k = (e >> 4) * 32 + ((e & 15) >> 2) * 8 + g * 4 + (e & 3);
-    if (mv_visible_iv(i, j0 + k, om[k], iv_ptr, iv)) bits |= 1u << e;
+// Rows [r0, r0 + 32) that lie in the live interval [b, e), as bits.
+__device__ __forceinline__ uint32_t mv_row_bits(int b, int e, int r0) {
+  const int l = max(b - r0, 0), h = min(e - r0, 32);
+  return h > l ? (0xffffffffu << (l & 31)) & (0xffffffffu >> ((32 - h) & 31)) : 0u;
+}
+
+// Rows [r0, r0 + 32) that see key j: its first interval and its further ones
+// (each list entry is read once for 32 rows, not once per score element).
+__device__ __forceinline__ uint32_t mv_key_row_bits(int j, int omega_j, int r0, const int* iv_ptr,
+                                                    const int* iv) {
+  uint32_t bits = mv_row_bits(j, mv_first_end(omega_j), r0);
+  if (omega_j < 0) {
+    const int e = iv_ptr[j + 1];
+    for (int k = iv_ptr[j]; k < e; ++k) bits |= mv_row_bits(iv[2 * k], iv[2 * k + 1], r0);
   }
   return bits;
 }
