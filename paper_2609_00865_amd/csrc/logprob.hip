@@ -23,8 +23,17 @@
 // SIMD) in a 2 x 4 grid over a 256 A-row x 256 token tile; each wave owns 128
 // A rows x 64 tokens and runs MFMA 16x16x32.  64-wide k slices go from HBM
 // straight into LDS (global_load_lds: no register staging and no LDS store
-// instructions), two slices in flight, one barrier per slice; the next k
-// step's operand fragments are read while the current step's MFMAs run.  An
+// instructions), two slices deep.  The two waves of a SIMD take turns: one
+// runs the MFMAs of a quarter of its tile while the other reads its next
+// fragments from LDS and issues its share of a later slice's loads, so the
+// matrix pipe is not waiting behind LDS reads, and quarter by quarter the
+// slice's LDS regions are free for the slice after next (a load has 1.5
+// slices to land).  Bound by the matrix pipe at the clock the chip holds
+// under it: at 32768 tokens x 3584 x 152064 the pipe is busy 83% (logits),
+// 75% (G) and 93% (dH) of the cycles at 1.63-1.8 GHz, where the earlier loop
+// (both waves reading, then both in MFMAs; one barrier per slice) had
+// 56-64%.  At 4001 tokens: logits 3.60 -> 3.18 ms, G 3.74 -> 3.23, dH 3.54 ->
+// 3.09; at 32768: 26.8 -> 26.7, 28.7 -> 26.8, 26.4 -> 24.0 ms.  An
 // operand slice sits in LDS as [256 rows][64] bf16 without padding, with
 // 16-byte chunk c of row r at chunk position c ^ (r & 7): the fragment reads
 // (16 lanes = 16 consecutive rows at one chunk) hit distinct banks.  Tiles are
@@ -32,6 +41,7 @@
 // patch (a few token tiles x several A tiles) and share operand slices in that
 // XCD's L2.
 #include <algorithm>
+#include <type_traits>
 
 #include "mv_grpo_dev.h"
 
@@ -48,7 +58,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.69314718055994531f;
 // tile engine
 constexpr int SLICE_B = 256 * BKK * 2;             // bytes of one operand's k slice
-constexpr int NLD = SLICE_B / 1024 / NWAVES;       // direct loads per operand, thread and slice
+constexpr int NLD = SLICE_B / 1024 / NWAVES;       // dW: direct loads per operand, thread and slice
 
 // Panel layout of a bf16 matrix [R][K] (R padded to a multiple of 256, K a
 // multiple of 64), used for G and W^T, the operands of the dH product whose
@@ -146,68 +156,84 @@ __global__ __launch_bounds__(NWAVES * 64, 1) void lm_tile_kernel(LmArgs a) {
   const int kbeg = (MODE == kModeDh) ? split * a.nk_split : 0;
   const int nk = (MODE == kModeDh) ? min(K / BKK - kbeg, a.nk_split) : K / BKK;
 
-  // Load i of this wave fills 16-byte slots (i * NWAVES + wave) * 64 + lane of
-  // each operand's slice: row s / 8, k chunk (s % 8) ^ (row & 7).  Rows past
-  // the operands are read from clamped (valid) rows; their products land in
+  // Slice loads.  Each operand slice is loaded in two regions of 128 rows,
+  // the rows that every wave's first (region 0) and second (1) half of its
+  // fragments come from: A rows 64 of each 128, token rows 32 of each 64.
+  // Load q of this wave fills rows rowX(h, q) + lane / 8, whose 16-byte chunk
+  // position lane % 8 holds chunk (lane % 8) ^ (row % 8).  Rows past the
+  // operands are read from clamped (valid) rows; their products land in
   // output rows or columns that the epilogues skip.  The dH product reads
   // both operands (W^T and G) in the panel layout, the others row-major.
   constexpr bool PANELS = MODE == kModeDh;
-  constexpr int SSTEP = PANELS ? PANEL : BKK;   // elements from one k slice of a row to the next
-  const u16* srcA[NLD];
-  const u16* srcB[NLD];
+  constexpr bool GATHER = MODE == kModeKL || MODE == kModeKLGrad;
+  constexpr uint32_t SSTEP = (PANELS ? PANEL : BKK) * 2;   // bytes from a row's k slice to the next
+  auto row_a = [&](int h, int q) { return q * 128 + h * 64 + wave * 8; };
+  auto row_b = [&](int h, int q) { return q * 128 + (wave >> 2) * 64 + h * 32 + (wave & 3) * 8; };
+  const size_t tile_a = PANELS ? panel_index(a0, kbeg * BKK, K) : size_t(a0) * K;
+  const size_t tile_b = PANELS ? panel_index(t0, kbeg * BKK, K) : size_t(t0) * K;
+  const char* baseA = reinterpret_cast<const char*>(uniform_ptr(A + tile_a));
+  const char* baseB =
+      GATHER ? nullptr : reinterpret_cast<const char*>(uniform_ptr((PANELS ? a.G : a.h) + tile_b));
+  uint32_t offA[2][2], offB[2][2];
+  const u16* rowB[2][2];   // gathered token rows
+  const uint32_t row_bytes = PANELS ? BKK * 2 : uint32_t(K) * 2;
 #pragma unroll
-  for (int i = 0; i < NLD; ++i) {
-    const int s = (i * NWAVES + wave) * 64 + lane;
-    const int row = s >> 3, kc = (s & 7) ^ (row & 7);
-    const int ar = min(a0 + row, a_rows - 1);
-    const int t = min(t0 + row, a.T - 1);
-    if (PANELS) {
-      srcA[i] = A + panel_index(ar, kbeg * BKK, K) + kc * 8;
-      srcB[i] = a.G + panel_index(t, kbeg * BKK, K) + kc * 8;
-      continue;
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const uint32_t ch = ((lane & 7) ^ (lane >> 3)) * 16;
+      const int ra = min(row_a(h, q) + (lane >> 3), a_rows - 1 - a0);
+      const int rb = min(row_b(h, q) + (lane >> 3), a.T - 1 - t0);
+      offA[h][q] = uint32_t(ra) * row_bytes + ch;
+      offB[h][q] = uint32_t(rb) * row_bytes + ch;
+      if (GATHER) {
+        // a row index outside its matrix reads as a zero hidden state
+        const int t = t0 + rb;
+        const int r = (t & 1) ? a.rowsS[t >> 1] : a.rowsT[t >> 1];
+        const int n_rows = (t & 1) ? a.n_rows_S : a.n_rows_T;
+        rowB[h][q] = ((r >= 0 && r < n_rows) ? ((t & 1) ? a.hS : a.hT) + size_t(r) * a.H
+                                             : a.zero_row) + ch / 2;
+      }
     }
-    const size_t koff = size_t(kbeg) * BKK + kc * 8;
-    srcA[i] = A + size_t(ar) * K + koff;
-    const u16* brow;
-    if (MODE == kModeKL || MODE == kModeKLGrad) {
-      // a row index outside its matrix reads as a zero hidden state
-      const int r = (t & 1) ? a.rowsS[t >> 1] : a.rowsT[t >> 1];
-      const int n_rows = (t & 1) ? a.n_rows_S : a.n_rows_T;
-      brow = (r >= 0 && r < n_rows) ? ((t & 1) ? a.hS : a.hT) + size_t(r) * a.H : a.zero_row;
+  // LDS: A slice in buffer b at b * 32 KiB, B at 64 KiB + b * 32 KiB, rows of
+  // 128 bytes
+  const uint32_t lds0 = lds_addr(smem);
+  auto issue_a = [&](int h, int kk) {
+    const uint32_t st = lds0 + (kk & 1) * SLICE_B;
+    const char* b = baseA + size_t(kk) * SSTEP;
+    lds_load16s(b, offA[h][0], st + row_a(h, 0) * 128);
+    lds_load16s(b, offA[h][1], st + row_a(h, 1) * 128);
+  };
+  auto issue_b = [&](int h, int kk) {
+    const uint32_t st = lds0 + 2 * SLICE_B + (kk & 1) * SLICE_B;
+    if (GATHER) {
+      lds_load16(rowB[h][0] + size_t(kk) * BKK, st + row_b(h, 0) * 128);
+      lds_load16(rowB[h][1] + size_t(kk) * BKK, st + row_b(h, 1) * 128);
     } else {
-      brow = a.h + size_t(t) * a.H;
-    }
-    srcB[i] = brow + koff;
-  }
-  typedef __attribute__((address_space(3))) u16 lds_u16;
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u16*)smem;   // LDS byte address
-  auto issue = [&](int kk) {
-    const uint32_t st = lds0 + (kk & 1) * (2 * SLICE_B) + wave * 1024;
-#pragma unroll
-    for (int i = 0; i < NLD; ++i) {
-      lds_load16(srcA[i] + size_t(kk) * SSTEP, st + i * NWAVES * 1024);
-      lds_load16(srcB[i] + size_t(kk) * SSTEP, st + SLICE_B + i * NWAVES * 1024);
+      const char* b = baseB + size_t(kk) * SSTEP;
+      lds_load16s(b, offB[h][0], st + row_b(h, 0) * 128);
+      lds_load16s(b, offB[h][1], st + row_b(h, 1) * 128);
     }
   };
 
-  const char* lds = reinterpret_cast<const char*>(smem);
+  // Fragments of half h: 16 consecutive rows at one chunk per read
   const int frow = lane & 15, fk = lane >> 4;
-  bf16x8 fa[2][FA], fb[2][FB];
-  // operand fragments of k step ks (0 or 1) of slice kk into register set buf
-  auto read_frags = [&](int buf, int kk, int ks) {
-    const char* sA = lds + (kk & 1) * (2 * SLICE_B);
-    const char* sB = sA + SLICE_B;
-    const int kc = ks * 4 + fk;
+  uint32_t pa = lds0 + (wa * 128 + frow) * 128 + ((fk ^ (frow & 7)) * 16);
+  uint32_t pb = lds0 + 2 * SLICE_B + (wt * 64 + frow) * 128 + ((fk ^ (frow & 7)) * 16);
+  bf16x8 fa[2][2][FA / 2], fb[2][2][FB / 2];   // [half][k step][block]
+  auto read_a = [&](int h, uint32_t p) {
 #pragma unroll
-    for (int i = 0; i < FA; ++i) {
-      const int row = wa * 128 + i * 16 + frow;
-      fa[buf][i] = as_bf16x8(ld16(sA + (row * 8 + (kc ^ (row & 7))) * 16));
-    }
+    for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-    for (int j = 0; j < FB; ++j) {
-      const int row = wt * 64 + j * 16 + frow;
-      fb[buf][j] = as_bf16x8(ld16(sB + (row * 8 + (kc ^ (row & 7))) * 16));
-    }
+      for (int i = 0; i < FA / 2; ++i)
+        fa[h][ks][i] = lds_frag((p ^ (ks * 64)) + h * 8192 + i * 2048);
+  };
+  auto read_b = [&](int h, uint32_t p) {
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int j = 0; j < FB / 2; ++j)
+        fb[h][ks][j] = lds_frag((p ^ (ks * 64)) + h * 4096 + j * 2048);
   };
 
   f32x4 acc[FA][FB];
@@ -215,39 +241,103 @@ __global__ __launch_bounds__(NWAVES * 64, 1) void lm_tile_kernel(LmArgs a) {
   for (int i = 0; i < FA; ++i)
 #pragma unroll
     for (int j = 0; j < FB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  auto mma = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < FA; ++i)
-#pragma unroll
-      for (int j = 0; j < FB; ++j) acc[i][j] = mfma16(fa[buf][i], fb[buf][j], acc[i][j]);
-  };
 
-  issue(0);
+  // Waves w and w + 4 share a SIMD and take turns: between two barriers one
+  // runs the 16 MFMAs of a quarter tile (A half ha x token half hb, both k
+  // steps), the other loads: the fragments of its next quarter from LDS and
+  // its share of a region of the slice after next.  The four quarters of a
+  // slice go (0,0) (0,1) (1,1) (1,0); before them are read B0, B1, A1 and the
+  // next slice's A0, so a region is free for its next load one or two turns
+  // after it is read, and each load has about 12 turns (1.5 slices) to land.
+  auto mma = [&](int ha, int hb) {
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int i = 0; i < FA / 2; ++i)
+#pragma unroll
+        for (int j = 0; j < FB / 2; ++j)
+          acc[ha * (FA / 2) + i][hb * (FB / 2) + j] =
+              mfma16(fa[ha][ks][i], fb[hb][ks][j], acc[ha * (FA / 2) + i][hb * (FB / 2) + j]);
+    __builtin_amdgcn_s_setprio(0);
+  };
+  // end of a turn: this wave's LDS reads are done (their region may be
+  // overwritten after the barrier)
+  auto turn = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto loaded = [&]() { __builtin_amdgcn_s_waitcnt(0xC07F); };   // lgkmcnt(0)
+
+  // order of the loads: A0 B0 B1 A1 of slice 0, of slice 1, ...; two loads
+  // per region and wave, so waiting for all but 12 keeps the six youngest
+  // regions in flight
+  auto issue_slice = [&](int kk) {
+    issue_a(0, kk);
+    issue_b(0, kk);
+    issue_b(1, kk);
+    issue_a(1, kk);
+  };
+  issue_slice(0);
   if (nk > 1) {
-    issue(1);
-    wait_vmcnt<2 * NLD>();   // slice 0 landed, slice 1 may still be in flight
+    issue_slice(1);
+    wait_vmcnt<12>();   // A0, B0 of slice 0
   } else {
     wait_vmcnt<0>();
   }
   __syncthreads();
-  read_frags(0, 0, 0);
-  // (the last slice is peeled: a loop body without a path around the barrier
-  // lets the second MFMA group start without waiting for the reads behind it)
-  for (int kk = 0; kk + 1 < nk; ++kk) {
-    read_frags(1, kk, 1);
-    mma(0);
-    // slice kk + 1 is the only one in flight; after the barrier it is visible
-    // to every wave and every wave has read all of slice kk, whose buffer
-    // then takes slice kk + 2
-    wait_vmcnt<0>();
-    __syncthreads();
-    if (kk + 2 < nk) issue(kk + 2);
-    read_frags(0, kk + 1, 0);
-    mma(1);
-  }
-  read_frags(1, nk - 1, 1);
-  mma(0);
-  mma(1);
+  read_a(0, pa);
+  loaded();
+  turn();
+  if (wa == 1) turn();   // the second half of the waves runs one turn behind
+  // one slice; MORE: slice kk + 2 exists; W0 .. W3: loads that may stay in
+  // flight at each turn
+  auto slice = [&](int kk, auto more_tag, auto last_tag, auto w0, auto w1, auto w2, auto w3) {
+    constexpr bool MORE = decltype(more_tag)::value, LAST = decltype(last_tag)::value;
+    if (MORE) issue_a(0, kk + 2);
+    read_b(0, pb);
+    wait_vmcnt<decltype(w0)::value>();
+    loaded();
+    turn();
+    mma(0, 0);
+    turn();
+    if (MORE) issue_b(0, kk + 2);
+    read_b(1, pb);
+    wait_vmcnt<decltype(w1)::value>();
+    loaded();
+    turn();
+    mma(0, 1);
+    turn();
+    if (MORE) issue_b(1, kk + 2);
+    read_a(1, pa);
+    wait_vmcnt<decltype(w2)::value>();
+    loaded();
+    turn();
+    mma(1, 1);
+    turn();
+    const uint32_t flip = (kk & 1) ? uint32_t(-SLICE_B) : uint32_t(SLICE_B);
+    pa += flip;
+    pb += flip;
+    if (MORE) issue_a(1, kk + 2);
+    if (!LAST) read_a(0, pa);
+    wait_vmcnt<decltype(w3)::value>();
+    loaded();
+    turn();
+    mma(1, 0);
+    turn();
+  };
+  using std::integral_constant;
+  using T0 = std::true_type;
+  using F0 = std::false_type;
+  using n12 = integral_constant<int, 12>;
+  for (int kk = 0; kk + 2 < nk; ++kk) slice(kk, T0{}, F0{}, n12{}, n12{}, n12{}, n12{});
+  if (nk > 1)
+    slice(nk - 2, F0{}, F0{}, integral_constant<int, 10>{}, integral_constant<int, 8>{},
+          integral_constant<int, 6>{}, integral_constant<int, 4>{});
+  slice(nk - 1, F0{}, T0{}, integral_constant<int, 2>{}, integral_constant<int, 0>{},
+        integral_constant<int, 0>{}, integral_constant<int, 0>{});
+  if (wa == 0) turn();
 
   // acc[i][j][r]: A row rb + i*16 + r, token tb + j*16
   const int rb = a0 + wa * 128 + (lane >> 4) * 4;

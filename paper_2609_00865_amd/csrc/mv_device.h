@@ -54,6 +54,17 @@ __device__ __forceinline__ void lds_load16(const void* src, uint32_t lds) {
       : "memory");
 }
 
+// The same with a wave-uniform base address and a byte offset per lane.
+__device__ __forceinline__ void lds_load16s(const void* base, uint32_t off, uint32_t lds) {
+  uint32_t saved;
+  asm volatile(
+      "s_mov_b32 %0, m0\n\ts_mov_b32 m0, %3\n\tglobal_load_lds_dwordx4 %1, %2\n\t"
+      "s_mov_b32 m0, %0"
+      : "=&s"(saved)
+      : "v"(off), "s"(base), "s"(__builtin_amdgcn_readfirstlane(lds))
+      : "memory");
+}
+
 // A wave-uniform pointer taken through readfirstlane, so that it is held in
 // scalar registers (the inline asm below takes scalar operands; the compiler
 // may otherwise keep a uniform value in vector registers).
@@ -252,6 +263,12 @@ struct KvTileLoader {
     }
   }
 };
+
+// 16 bytes at an LDS byte address as an MFMA operand
+__device__ __forceinline__ bf16x8 lds_frag(uint32_t addr) {
+  typedef __attribute__((address_space(3))) const bf16x8 lds_bf16x8;
+  return *(lds_bf16x8*)(uintptr_t)addr;
+}
 
 // LDS byte address of a __shared__ object
 template <typename X>
