@@ -33,7 +33,7 @@
 // 75% (G) and 93% (dH) of the cycles at 1.63-1.8 GHz, where the earlier loop
 // (both waves reading, then both in MFMAs; one barrier per slice) had
 // 56-64%.  At 4001 tokens: logits 3.60 -> 3.18 ms, G 3.74 -> 3.23, dH 3.54 ->
-// 3.09; at 32768: 26.8 -> 26.7, 28.7 -> 26.8, 26.4 -> 24.0 ms.  An
+// 3.09; at 32768: 26.1 -> 23.5, 27.8 -> 24.9, 25.7 -> 22.7 ms.  An
 // operand slice sits in LDS as [256 rows][64] bf16 without padding, with
 // 16-byte chunk c of row r at chunk position c ^ (r & 7): the fragment reads
 // (16 lanes = 16 consecutive rows at one chunk) hit distinct banks.  Tiles are
@@ -58,7 +58,6 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.69314718055994531f;
 // tile engine
 constexpr int SLICE_B = 256 * BKK * 2;             // bytes of one operand's k slice
-constexpr int NLD = SLICE_B / 1024 / NWAVES;       // dW: direct loads per operand, thread and slice
 
 // Panel layout of a bf16 matrix [R][K] (R padded to a multiple of 256, K a
 // multiple of 64), used for G and W^T, the operands of the dH product whose
@@ -70,7 +69,7 @@ __host__ __device__ inline size_t panel_index(int r, int k, int K) {
   return (size_t(r >> 8) * (K >> 6) + (k >> 6)) * PANEL + (r & 255) * 64 + (k & 63);
 }
 constexpr int FA = 8, FB = 4;                      // 16-row MFMA blocks per wave: A rows, tokens
-static_assert(NLD * NWAVES * 1024 == SLICE_B, "slice split over the waves");
+static_assert(4 * NWAVES * 1024 == SLICE_B, "two regions of two 1 KiB loads per wave");
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 int vocab_pad(int V) { return (V + BA - 1) / BA * BA; }
 }  // namespace
@@ -136,6 +135,97 @@ __device__ __forceinline__ bool tile_of(const LmArgs& a, int n_splits, int& a0, 
   a0 = (rem / t_in) * BA;
   t0 = (grp * GT + rem % t_in) * BT;
   return true;
+}
+
+// The k loop of a 256 x 256 tile over nk >= 1 slices of 64.  Waves w and w + 4
+// share a SIMD and take turns: between two barriers one runs the MFMAs of a
+// quarter of its tile (mma(ha, hb): half ha of its A fragments x half hb of
+// its B fragments, 256 cycles), the other loads: the fragments of its next
+// quarter from LDS (read_a / read_b of a half, from the current buffer) and
+// its share (two loads) of a region of the slice after next (issue_a /
+// issue_b(half, slice)).  A region is the part of an operand slice that the
+// waves' fragments of one half come from.  The quarters of a slice go (0,0)
+// (0,1) (1,1) (1,0); before them are read B0, B1, A1 and the next slice's A0
+// (flip(d) moves the fragment addresses to the other buffer), so a region is
+// free for its next load one or two turns after it is read, and each load has
+// about 12 turns (1.5 slices) to land.  late: this wave runs one turn behind.
+// On return every load has landed and every wave is done with the LDS reads.
+template <class IA, class IB, class RA, class RB, class FL, class MM>
+__device__ __forceinline__ void tile_pipeline(int nk, bool late, IA issue_a, IB issue_b, RA read_a,
+                                              RB read_b, FL flip, MM mma) {
+  auto turn = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // before the barrier that ends a load turn: the wave's LDS reads are done
+  // (their region may be overwritten), the loads the next turns read landed
+  auto read_done = [&]() { __builtin_amdgcn_s_waitcnt(0xC07F); };   // lgkmcnt(0)
+  auto quarter = [&](int ha, int hb) {
+    turn();
+    __builtin_amdgcn_s_setprio(1);
+    mma(ha, hb);
+    __builtin_amdgcn_s_setprio(0);
+    turn();
+  };
+  // order of the loads: A0 B0 B1 A1 of slice 0, of slice 1, ...; two loads
+  // per region and wave, so waiting for all but 12 keeps the six youngest
+  // regions in flight
+  auto issue_slice = [&](int kk) {
+    issue_a(0, kk);
+    issue_b(0, kk);
+    issue_b(1, kk);
+    issue_a(1, kk);
+  };
+  issue_slice(0);
+  if (nk > 1) {
+    issue_slice(1);
+    wait_vmcnt<12>();   // A0, B0 of slice 0
+  } else {
+    wait_vmcnt<0>();
+  }
+  __syncthreads();
+  read_a(0);
+  read_done();
+  turn();
+  if (late) turn();
+  // one slice; MORE: slice kk + 2 exists; w0 .. w3: loads that may stay in
+  // flight at each turn
+  auto slice = [&](int kk, auto more_tag, auto last_tag, auto w0, auto w1, auto w2, auto w3) {
+    constexpr bool MORE = decltype(more_tag)::value, LAST = decltype(last_tag)::value;
+    if (MORE) issue_a(0, kk + 2);
+    read_b(0);
+    wait_vmcnt<decltype(w0)::value>();
+    read_done();
+    quarter(0, 0);
+    if (MORE) issue_b(0, kk + 2);
+    read_b(1);
+    wait_vmcnt<decltype(w1)::value>();
+    read_done();
+    quarter(0, 1);
+    if (MORE) issue_b(1, kk + 2);
+    read_a(1);
+    wait_vmcnt<decltype(w2)::value>();
+    read_done();
+    quarter(1, 1);
+    flip((kk & 1) ? uint32_t(-SLICE_B) : uint32_t(SLICE_B));
+    if (MORE) issue_a(1, kk + 2);
+    if (!LAST) read_a(0);
+    wait_vmcnt<decltype(w3)::value>();
+    read_done();
+    quarter(1, 0);
+  };
+  using std::integral_constant;
+  using T = std::true_type;
+  using F = std::false_type;
+  using n12 = integral_constant<int, 12>;
+  for (int kk = 0; kk + 2 < nk; ++kk) slice(kk, T{}, F{}, n12{}, n12{}, n12{}, n12{});
+  if (nk > 1)
+    slice(nk - 2, F{}, F{}, integral_constant<int, 10>{}, integral_constant<int, 8>{},
+          integral_constant<int, 6>{}, integral_constant<int, 4>{});
+  slice(nk - 1, F{}, T{}, integral_constant<int, 2>{}, integral_constant<int, 0>{},
+        integral_constant<int, 0>{}, integral_constant<int, 0>{});
+  if (!late) turn();
 }
 
 template <int MODE>
@@ -242,15 +332,7 @@ __global__ __launch_bounds__(NWAVES * 64, 1) void lm_tile_kernel(LmArgs a) {
 #pragma unroll
     for (int j = 0; j < FB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // Waves w and w + 4 share a SIMD and take turns: between two barriers one
-  // runs the 16 MFMAs of a quarter tile (A half ha x token half hb, both k
-  // steps), the other loads: the fragments of its next quarter from LDS and
-  // its share of a region of the slice after next.  The four quarters of a
-  // slice go (0,0) (0,1) (1,1) (1,0); before them are read B0, B1, A1 and the
-  // next slice's A0, so a region is free for its next load one or two turns
-  // after it is read, and each load has about 12 turns (1.5 slices) to land.
   auto mma = [&](int ha, int hb) {
-    __builtin_amdgcn_s_setprio(1);
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
@@ -259,85 +341,13 @@ __global__ __launch_bounds__(NWAVES * 64, 1) void lm_tile_kernel(LmArgs a) {
         for (int j = 0; j < FB / 2; ++j)
           acc[ha * (FA / 2) + i][hb * (FB / 2) + j] =
               mfma16(fa[ha][ks][i], fb[hb][ks][j], acc[ha * (FA / 2) + i][hb * (FB / 2) + j]);
-    __builtin_amdgcn_s_setprio(0);
   };
-  // end of a turn: this wave's LDS reads are done (their region may be
-  // overwritten after the barrier)
-  auto turn = [&]() {
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_sched_barrier(0);
+  auto flip = [&](uint32_t d) {
+    pa += d;
+    pb += d;
   };
-  auto loaded = [&]() { __builtin_amdgcn_s_waitcnt(0xC07F); };   // lgkmcnt(0)
-
-  // order of the loads: A0 B0 B1 A1 of slice 0, of slice 1, ...; two loads
-  // per region and wave, so waiting for all but 12 keeps the six youngest
-  // regions in flight
-  auto issue_slice = [&](int kk) {
-    issue_a(0, kk);
-    issue_b(0, kk);
-    issue_b(1, kk);
-    issue_a(1, kk);
-  };
-  issue_slice(0);
-  if (nk > 1) {
-    issue_slice(1);
-    wait_vmcnt<12>();   // A0, B0 of slice 0
-  } else {
-    wait_vmcnt<0>();
-  }
-  __syncthreads();
-  read_a(0, pa);
-  loaded();
-  turn();
-  if (wa == 1) turn();   // the second half of the waves runs one turn behind
-  // one slice; MORE: slice kk + 2 exists; W0 .. W3: loads that may stay in
-  // flight at each turn
-  auto slice = [&](int kk, auto more_tag, auto last_tag, auto w0, auto w1, auto w2, auto w3) {
-    constexpr bool MORE = decltype(more_tag)::value, LAST = decltype(last_tag)::value;
-    if (MORE) issue_a(0, kk + 2);
-    read_b(0, pb);
-    wait_vmcnt<decltype(w0)::value>();
-    loaded();
-    turn();
-    mma(0, 0);
-    turn();
-    if (MORE) issue_b(0, kk + 2);
-    read_b(1, pb);
-    wait_vmcnt<decltype(w1)::value>();
-    loaded();
-    turn();
-    mma(0, 1);
-    turn();
-    if (MORE) issue_b(1, kk + 2);
-    read_a(1, pa);
-    wait_vmcnt<decltype(w2)::value>();
-    loaded();
-    turn();
-    mma(1, 1);
-    turn();
-    const uint32_t flip = (kk & 1) ? uint32_t(-SLICE_B) : uint32_t(SLICE_B);
-    pa += flip;
-    pb += flip;
-    if (MORE) issue_a(1, kk + 2);
-    if (!LAST) read_a(0, pa);
-    wait_vmcnt<decltype(w3)::value>();
-    loaded();
-    turn();
-    mma(1, 0);
-    turn();
-  };
-  using std::integral_constant;
-  using T0 = std::true_type;
-  using F0 = std::false_type;
-  using n12 = integral_constant<int, 12>;
-  for (int kk = 0; kk + 2 < nk; ++kk) slice(kk, T0{}, F0{}, n12{}, n12{}, n12{}, n12{});
-  if (nk > 1)
-    slice(nk - 2, F0{}, F0{}, integral_constant<int, 10>{}, integral_constant<int, 8>{},
-          integral_constant<int, 6>{}, integral_constant<int, 4>{});
-  slice(nk - 1, F0{}, T0{}, integral_constant<int, 2>{}, integral_constant<int, 0>{},
-        integral_constant<int, 0>{}, integral_constant<int, 0>{});
-  if (wa == 0) turn();
+  tile_pipeline(nk, wa == 1, issue_a, issue_b, [&](int h) { read_a(h, pa); },
+                [&](int h) { read_b(h, pb); }, flip, mma);
 
   // acc[i][j][r]: A row rb + i*16 + r, token tb + j*16
   const int rb = a0 + wa * 128 + (lane >> 4) * 4;
@@ -516,130 +526,115 @@ __global__ __launch_bounds__(NWAVES * 64, 1) void lm_tile_kernel(LmArgs a) {
   }
 }
 
-// dW[v][c] = sum_t G[t][v] H[t][c] (fp32 out).  Same tile shape as the tile
-// engine (256 vocabulary rows x 256 hidden columns, 8 waves of 128 x 64) with
+// dW[v][c] = sum_t G[t][v] H[t][c] (fp32 out).  Same tile shape and pipeline
+// as the tile engine (256 vocabulary rows x 256 hidden columns, 8 waves) with
 // MFMA 32x32x16; k = tokens, along which neither operand is contiguous.  Both
-// k slices ([64 tokens][256]) go from HBM straight into LDS, two in flight,
-// as unpadded 512-byte rows with 16-byte chunk c of token row r at position
-// c ^ ((r & 3) << 2): the transposing operand reads (four token rows x 64
-// bytes per 32 lanes) then hit distinct banks.  G's rows are padded with zeros
-// to a multiple of 64 tokens (the grad pass writes them), so the last slice
-// needs no masking: H rows past T are read clamped and meet zero G rows.
+// k slices (64 tokens x 256 columns) go from HBM straight into LDS as four
+// sub-tiles of 64 columns: 128-byte token rows, with 16-byte chunk c of row r
+// at position c ^ ((r & 2) << 1), so that a transposing operand read (four
+// token rows x 64 bytes per 32 lanes) hits distinct banks.  A wave owns 128
+// vocabulary rows (two sub-tiles, its two halves) and the columns wt * 32 of
+// each 128 (its two halves).  G's rows past T are zeros up to a multiple of
+// 256 (the grad pass writes them), so the last slice needs no masking: H rows
+// past T are read clamped and meet zero G rows.  Bound as the tile engine: at
+// 32768 tokens x 3584 x 152064 the loop in which both waves of a SIMD read and
+// multiplied together took 30.9 ms with the pipe 64% busy, this one 26.6 ms.
 __global__ __launch_bounds__(NWAVES * 64, 1) void lm_dw_kernel(LmArgs a) {
-  constexpr int WC = BT / (NWAVES / 2);    // hidden columns per wave (64)
-  constexpr int NJ = WC / 32;
-  __shared__ __align__(1024) u16 smem[2 * 2 * SLICE_B / 2];   // 2 slices x (G, H)
+  __shared__ __align__(1024) u16 smem[2 * 2 * SLICE_B / 2];   // (G, H) x 2 slices
+  constexpr int SUB = 64 * 128;   // bytes of a sub-tile
 
   int a0, t0, split;
   if (!tile_of<GROUP_T_V>(a, 1, a0, t0, split)) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int c = lane & 31, g = lane >> 5;
-  const int wa = wave / (NWAVES / 2), wt = wave % (NWAVES / 2);
-  const int nk = a.Tg / BKK;
+  const int wa = wave >> 2, wt = wave & 3;
+  const int nk = (a.T + BKK - 1) / BKK;
 
-  // load i of this wave fills 16-byte slots (i * NWAVES + wave) * 64 + lane:
-  // token row s / 32, chunk (s % 32) ^ ((row & 3) << 2)
-  int gcol[NLD], hrow[NLD], hcol[NLD];
+  // Region h of G: the sub-tiles h and h + 2 (half h of the waves' rows), of H:
+  // the sub-tiles 2 h and 2 h + 1 (half h of their columns).  Load q of this
+  // wave fills rows wave * 8 + lane / 8 of the region's sub-tile q.
+  const uint32_t lds0 = lds_addr(smem);
+  const int lrow = wave * 8 + (lane >> 3);
+  const uint32_t lch = ((lane & 7) ^ ((lrow & 2) << 1)) * 16;
+  const uint32_t goff = lrow * 128 + lch;
+  const uint32_t hrow_bytes = uint32_t(a.H) * 2;
+  const char* Gb = reinterpret_cast<const char*>(uniform_ptr(a.G + panel_index(0, a0, a.Vp)));
+  const size_t gstep = size_t(a.Vp >> 6) * PANEL * 2;   // bytes from 256 token rows to the next
+  const char* Hb = reinterpret_cast<const char*>(uniform_ptr(a.h));
+  auto issue_a = [&](int h, int kk) {
+    const char* b = Gb + size_t(kk >> 2) * gstep + (kk & 3) * SUB;
+    const uint32_t st = lds0 + (kk & 1) * SLICE_B + wave * 1024;
+    lds_load16s(b + size_t(h) * (PANEL * 2), goff, st + h * SUB);
+    lds_load16s(b + size_t(h + 2) * (PANEL * 2), goff, st + (h + 2) * SUB);
+  };
+  auto issue_b = [&](int h, int kk) {
+    const int k0 = kk * BKK;   // < T
+    const uint32_t off = uint32_t(min(lrow, a.T - 1 - k0)) * hrow_bytes + lch;
+    const uint32_t st = lds0 + 2 * SLICE_B + (kk & 1) * SLICE_B + wave * 1024;
+    // hidden columns past H (whole sub-tiles) read the last ones: outputs skipped
 #pragma unroll
-  for (int i = 0; i < NLD; ++i) {
-    const int s = (i * NWAVES + wave) * 64 + lane;
-    const int row = s >> 5, ch = (s & 31) ^ ((row & 3) << 2);
-    gcol[i] = a0 + ch * 8;
-    hrow[i] = row;
-    hcol[i] = min(t0 + ch * 8, a.H - 8);   // hidden columns past H: outputs skipped
-  }
-  typedef __attribute__((address_space(3))) u16 lds_u16;
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u16*)smem;
-  auto issue = [&](int kk) {
-    const uint32_t st = lds0 + (kk & 1) * (2 * SLICE_B) + wave * 1024;
-    const int k0 = kk * BKK;
-#pragma unroll
-    for (int i = 0; i < NLD; ++i) {
-      lds_load16(a.G + panel_index(k0 + hrow[i], gcol[i], a.Vp), st + i * NWAVES * 1024);
-      const int t = min(k0 + hrow[i], a.T - 1);
-      lds_load16(a.h + size_t(t) * a.H + hcol[i], st + SLICE_B + i * NWAVES * 1024);
-    }
+    for (int q = 0; q < 2; ++q)
+      lds_load16s(Hb + size_t(k0) * hrow_bytes + min(t0 + (2 * h + q) * 64, a.H - 64) * 2, off,
+                  st + (2 * h + q) * SUB);
   };
 
-  // transposing operand read in natural k order (rows g*8 + 0..7): lane l of a
-  // 16-lane group reads token rows rb + (lane/32)*8 + l/4 and + 4, columns
-  // col0 + ((lane/16) % 2)*16 + 4 (l % 4); with rb a multiple of 16 and col0 a
-  // multiple of 32 the swizzle term of a lane is fixed
+  // Transposing operand read in natural k order (rows g*8 + 0..7 of a k step
+  // of 16): lane l of a 16-lane group reads token rows (lane/32)*8 + l/4 and +
+  // 4, columns col0 + ((lane/16) % 2)*16 + 4 (l % 4); the swizzle term of a
+  // lane is fixed (row & 2 = (l / 4) & 2), and col0 = 32 is chunk bit 2.
   const int l = lane & 15;
   const int rl = (lane >> 5) * 8 + (l >> 2);
-  const int fl = (l >> 2) & 3;
-  const int cl = ((((lane >> 4) & 1) * 2 + ((l & 3) >> 1)) << 3) + ((4 * (l & 3)) & 7);
-  const char* lds = reinterpret_cast<const char*>(smem);
-  auto tr = [&](const u16* tile, int rb, int cg) {   // cg = col0 / 32
-    const u16* p0 = tile + (rb + rl) * 256 + (((cg ^ fl) << 5) + cl);
-    const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(p0));
-    const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(p0 + 4 * 256));
+  const uint32_t fr = rl * 128 +
+                      (((((lane >> 4) & 1) * 2 + ((l & 3) >> 1)) ^ ((rl & 2) << 1)) << 4) +
+                      (l & 1) * 8;
+  uint32_t pa = lds0 + wa * 2 * SUB + fr;
+  uint32_t pb = lds0 + 2 * SLICE_B + (wt >> 1) * SUB + (fr ^ ((wt & 1) * 64));
+  auto tr = [&](uint32_t p) {
+    const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(uintptr_t)p);
+    const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(uintptr_t)(p + 4 * 128));
     typedef short i16x8 __attribute__((ext_vector_type(8)));
     const i16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
     return __builtin_bit_cast(bf16x8, v);
   };
-  bf16x8 af[2][4], bfr[2][NJ];
-  auto read_frags = [&](int buf, int kk, int ks) {
-    const u16* sG = reinterpret_cast<const u16*>(lds + (kk & 1) * (2 * SLICE_B));
-    const u16* sH = reinterpret_cast<const u16*>(lds + (kk & 1) * (2 * SLICE_B) + SLICE_B);
+  bf16x8 fa[2][4][2], fb[2][4];   // [half][k step](block)
+  auto read_a = [&](int h) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) af[buf][i] = tr(sG, ks * 16, wa * 4 + i);
+    for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) bfr[buf][j] = tr(sH, ks * 16, wt * NJ + j);
+      for (int i = 0; i < 2; ++i) fa[h][ks][i] = tr((pa ^ (i * 64)) + h * SUB + ks * 16 * 128);
+  };
+  auto read_b = [&](int h) {
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) fb[h][ks] = tr(pb + h * 2 * SUB + ks * 16 * 128);
+  };
+  auto flip = [&](uint32_t d) {
+    pa += d;
+    pb += d;
   };
 
-  f32x16 acc[4][NJ];
+  f32x16 acc[4][2];
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < NJ; ++j)
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-  auto mma = [&](int buf) {
+  auto mma = [&](int ha, int hb) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) acc[i][j] = mfma32(af[buf][i], bfr[buf][j], acc[i][j]);
+      for (int i = 0; i < 2; ++i)
+        acc[ha * 2 + i][hb] = mfma32(fa[ha][ks][i], fb[hb][ks], acc[ha * 2 + i][hb]);
   };
-
-  // four 16-token k steps per slice; one barrier per slice (as in the tile engine)
-  issue(0);
-  if (nk > 1) {
-    issue(1);
-    wait_vmcnt<2 * NLD>();
-  } else {
-    wait_vmcnt<0>();
-  }
-  __syncthreads();
-  read_frags(0, 0, 0);
-  for (int kk = 0; kk + 1 < nk; ++kk) {
-    read_frags(1, kk, 1);
-    mma(0);
-    read_frags(0, kk, 2);
-    mma(1);
-    read_frags(1, kk, 3);
-    mma(0);
-    wait_vmcnt<0>();
-    __syncthreads();
-    if (kk + 2 < nk) issue(kk + 2);
-    read_frags(0, kk + 1, 0);
-    mma(1);
-  }
-  read_frags(1, nk - 1, 1);
-  mma(0);
-  read_frags(0, nk - 1, 2);
-  mma(1);
-  read_frags(1, nk - 1, 3);
-  mma(0);
-  mma(1);
+  tile_pipeline(nk, wa == 1, issue_a, issue_b, read_a, read_b, flip, mma);
 
   // acc[i][j][r]: vocabulary row a0 + wa*128 + i*32 + (r/4)*8 + g*4 + r%4,
-  //               hidden column t0 + wt*WC + j*32 + c
+  //               hidden column t0 + j*128 + wt*32 + c
+  const int c = lane & 31, g = lane >> 5;
   const int arow0 = a0 + wa * 128;
 #pragma unroll
-  for (int j = 0; j < NJ; ++j) {
-    const int hc = t0 + wt * WC + j * 32 + c;
+  for (int j = 0; j < 2; ++j) {
+    const int hc = t0 + j * 128 + wt * 32 + c;
     if (hc >= a.H) continue;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -1203,7 +1198,6 @@ hipError_t launch_logprob_dweight(int T, int H, int V, const void* hidden, const
   a.G = reinterpret_cast<const u16*>(align_ptr(const_cast<void*>(ws)) + kStatusBytes);
   a.dw = dw;
   a.T = T;
-  a.Tg = g_rows(T);
   a.H = H;
   a.V = V;
   a.Vp = vocab_pad(V);
