@@ -14,7 +14,9 @@
 // G_tv = g_t (onehot(y_t)_v - softmax(z_t)_v), stored once in bf16 (the tile
 // writes -g_t softmax(z_t)_v everywhere, the per-token pass then rewrites the
 // target entry), and a second pass of the same engine computes dH = G W from
-// a transposed copy of W, so that both operands run along the vocabulary.
+// a transposed copy of W, so that both operands run along the vocabulary (for
+// few tokens, where that copy is a large part of the call, from W itself,
+// read across its rows).
 // dW = G^T H contracts over tokens, along which neither operand is
 // contiguous: it has an engine of its own that stages both operands k-major
 // and reads them with the transposing LDS read.
@@ -49,6 +51,12 @@ namespace mv {
 
 namespace {
 constexpr int BA = 256, BT = 256, BKK = 64;
+// dH reads W itself up to this many tokens: the transposed copy costs its one
+// pass over W whatever the tokens (0.40 ms at 152064 x 3584), the product on
+// it runs 13% faster (4001 tokens: 3.09 against 3.53 ms; 1384 leaves: 1.12
+// against 1.30 ms; 32768 tokens: 22.7 against 25.9 ms).
+constexpr int kMaxDirectDh = 3072;
+constexpr int kMaxDhSplits = 32;           // fp32 partials of a dH product split over the vocabulary
 constexpr int NWAVES = 8;                  // waves per tile (2 x 4 grid)
 // token tiles per raster group: 8 x 4 A tiles run side by side on an XCD
 // for the products over the hidden dimension (measured ~1% faster than
@@ -74,7 +82,7 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 int vocab_pad(int V) { return (V + BA - 1) / BA * BA; }
 }  // namespace
 
-enum { kModeLogits = 0, kModeGrad = 1, kModeDh = 2, kModeKL = 3, kModeKLGrad = 4 };
+enum { kModeLogits = 0, kModeGrad = 1, kModeDh = 2, kModeKL = 3, kModeKLGrad = 4, kModeDhW = 5 };
 
 hipError_t launch_grpo_fused_finish(const float* part, int n_blocks, int stride, int n_traj,
                                     const float* adv, float* stats, hipStream_t stream);
@@ -233,18 +241,21 @@ __global__ __launch_bounds__(NWAVES * 64, 1) void lm_tile_kernel(LmArgs a) {
   __shared__ __align__(1024) u16 smem[2 * 2 * SLICE_B / 2];   // 2 slices x 2 operands
 
   int a0, t0, split;
-  constexpr int GT = MODE == kModeDh ? GROUP_T_V : GROUP_T_H;
-  if (!tile_of<GT>(a, MODE == kModeDh ? a.k_split : 1, a0, t0, split)) return;
+  constexpr bool DH = MODE == kModeDh || MODE == kModeDhW;
+  constexpr int GT = DH ? GROUP_T_V : GROUP_T_H;
+  if (!tile_of<GT>(a, DH ? a.k_split : 1, a0, t0, split)) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wa = wave >> 2, wt = wave & 3;
 
-  // A [a_rows][K] and B [T][K], both contiguous along k
-  const int K = (MODE == kModeDh) ? a.Vp : a.H;
-  const int a_rows = (MODE == kModeDh) ? a.H : a.V;
-  const u16* A = (MODE == kModeDh) ? a.wT : a.w;
-  const int kbeg = (MODE == kModeDh) ? split * a.nk_split : 0;
-  const int nk = (MODE == kModeDh) ? min(K / BKK - kbeg, a.nk_split) : K / BKK;
+  // A [a_rows][K] and B [T][K], both contiguous along k; kModeDhW: A is W
+  // itself, [K][a_rows]
+  constexpr bool TRA = MODE == kModeDhW;
+  const int K = DH ? a.Vp : a.H;
+  const int a_rows = DH ? a.H : a.V;
+  const u16* A = MODE == kModeDh ? a.wT : a.w;
+  const int kbeg = DH ? split * a.nk_split : 0;
+  const int nk = DH ? min((a.V + BKK - 1) / BKK - kbeg, a.nk_split) : K / BKK;
 
   // Slice loads.  Each operand slice is loaded in two regions of 128 rows,
   // the rows that every wave's first (region 0) and second (1) half of its
@@ -253,13 +264,17 @@ __global__ __launch_bounds__(NWAVES * 64, 1) void lm_tile_kernel(LmArgs a) {
   // position lane % 8 holds chunk (lane % 8) ^ (row % 8).  Rows past the
   // operands are read from clamped (valid) rows; their products land in
   // output rows or columns that the epilogues skip.  The dH product reads
-  // both operands (W^T and G) in the panel layout, the others row-major.
-  constexpr bool PANELS = MODE == kModeDh;
+  // G (and W^T) in the panel layout, the others row-major.
+  // kModeDhW: the regions of A are sub-tiles of 64 vocabulary rows x 64
+  // hidden columns, h and h + 2, in 128-byte rows with chunk c of row r at
+  // position c ^ ((r & 2) | (r & 8) / 2): a transposing fragment read (rows 0-3
+  // and 8-11 x 32 bytes per 32 lanes) hits distinct banks.
+  constexpr bool PANELS = DH;
   constexpr bool GATHER = MODE == kModeKL || MODE == kModeKLGrad;
   constexpr uint32_t SSTEP = (PANELS ? PANEL : BKK) * 2;   // bytes from a row's k slice to the next
   auto row_a = [&](int h, int q) { return q * 128 + h * 64 + wave * 8; };
   auto row_b = [&](int h, int q) { return q * 128 + (wave >> 2) * 64 + h * 32 + (wave & 3) * 8; };
-  const size_t tile_a = PANELS ? panel_index(a0, kbeg * BKK, K) : size_t(a0) * K;
+  const size_t tile_a = TRA ? size_t(0) : PANELS ? panel_index(a0, kbeg * BKK, K) : size_t(a0) * K;
   const size_t tile_b = PANELS ? panel_index(t0, kbeg * BKK, K) : size_t(t0) * K;
   const char* baseA = reinterpret_cast<const char*>(uniform_ptr(A + tile_a));
   const char* baseB =
@@ -285,11 +300,24 @@ __global__ __launch_bounds__(NWAVES * 64, 1) void lm_tile_kernel(LmArgs a) {
                                              : a.zero_row) + ch / 2;
       }
     }
+  const int lrow = wave * 8 + (lane >> 3);   // kModeDhW: this lane's row of a sub-tile
+  const uint32_t wch = ((lane & 7) ^ ((lrow & 2) | ((lrow & 8) >> 1))) * 16;
   // LDS: A slice in buffer b at b * 32 KiB, B at 64 KiB + b * 32 KiB, rows of
   // 128 bytes
   const uint32_t lds0 = lds_addr(smem);
   auto issue_a = [&](int h, int kk) {
     const uint32_t st = lds0 + (kk & 1) * SLICE_B;
+    if (TRA) {
+      // vocabulary rows past V read row V - 1 and meet zeros of G; hidden
+      // columns past H (whole sub-tiles) the last ones: outputs skipped
+      const int k0 = (kbeg + kk) * BKK;   // < V
+      const uint32_t off = uint32_t(min(lrow, a.V - 1 - k0)) * (uint32_t(a.H) * 2) + wch;
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+        lds_load16s(baseA + (size_t(k0) * a.H + min(a0 + (h + 2 * q) * 64, a.H - 64)) * 2, off,
+                    st + row_a(h, q) * 128);
+      return;
+    }
     const char* b = baseA + size_t(kk) * SSTEP;
     lds_load16s(b, offA[h][0], st + row_a(h, 0) * 128);
     lds_load16s(b, offA[h][1], st + row_a(h, 1) * 128);
@@ -309,6 +337,11 @@ __global__ __launch_bounds__(NWAVES * 64, 1) void lm_tile_kernel(LmArgs a) {
   // Fragments of half h: 16 consecutive rows at one chunk per read
   const int frow = lane & 15, fk = lane >> 4;
   uint32_t pa = lds0 + (wa * 128 + frow) * 128 + ((fk ^ (frow & 7)) * 16);
+  if (TRA) {   // lane j of a 16-lane group: row fk * 8 + j / 4 (and + 4), columns 4 (j % 4)
+    const int r = fk * 8 + (frow >> 2);
+    pa = lds0 + wa * 128 * 128 + r * 128 +
+         ((((frow & 3) >> 1) ^ ((r & 2) | ((r & 8) >> 1))) * 16) + (frow & 1) * 8;
+  }
   uint32_t pb = lds0 + 2 * SLICE_B + (wt * 64 + frow) * 128 + ((fk ^ (frow & 7)) * 16);
   bf16x8 fa[2][2][FA / 2], fb[2][2][FB / 2];   // [half][k step][block]
   auto read_a = [&](int h, uint32_t p) {
@@ -316,7 +349,8 @@ __global__ __launch_bounds__(NWAVES * 64, 1) void lm_tile_kernel(LmArgs a) {
     for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
       for (int i = 0; i < FA / 2; ++i)
-        fa[h][ks][i] = lds_frag((p ^ (ks * 64)) + h * 8192 + i * 2048);
+        fa[h][ks][i] = TRA ? lds_frag_tr((p ^ (i * 32)) + h * 8192 + ks * 32 * 128, 4 * 128)
+                           : lds_frag((p ^ (ks * 64)) + h * 8192 + i * 2048);
   };
   auto read_b = [&](int h, uint32_t p) {
 #pragma unroll
@@ -495,7 +529,7 @@ __global__ __launch_bounds__(NWAVES * 64, 1) void lm_tile_kernel(LmArgs a) {
         }
       }
     }
-  } else {  // kModeDh: A rows are hidden columns
+  } else {  // dH: A rows are hidden columns
 #pragma unroll
     for (int j = 0; j < FB; ++j) {
       const int t = tb + j * 16;
@@ -589,13 +623,7 @@ __global__ __launch_bounds__(NWAVES * 64, 1) void lm_dw_kernel(LmArgs a) {
                       (l & 1) * 8;
   uint32_t pa = lds0 + wa * 2 * SUB + fr;
   uint32_t pb = lds0 + 2 * SLICE_B + (wt >> 1) * SUB + (fr ^ ((wt & 1) * 64));
-  auto tr = [&](uint32_t p) {
-    const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(uintptr_t)p);
-    const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(uintptr_t)(p + 4 * 128));
-    typedef short i16x8 __attribute__((ext_vector_type(8)));
-    const i16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-    return __builtin_bit_cast(bf16x8, v);
-  };
+  auto tr = [&](uint32_t p) { return lds_frag_tr(p, 4 * 128); };
   bf16x8 fa[2][4][2], fb[2][4];   // [half][k step](block)
   auto read_a = [&](int h) {
 #pragma unroll
@@ -856,17 +884,22 @@ __global__ __launch_bounds__(256) void kl_combine_kernel(LmArgs a, float* kl, fl
 }
 
 // Vocabulary splits for a dH product: none when the output tiles already
-// cover the CUs several times, otherwise the count (<= 8) with the least time
-// per split slice, rounds of 256 resident blocks / splits (a larger count must
-// gain 5% to be taken: each split adds an fp32 partial to write and reduce).
-static int dh_splits(int n_tokens, int H) {
+// cover the CUs several times, otherwise the count with the least time, of
+// rounds of 256 resident blocks at 1.4 us a slice (a block's slice measured
+// 1.35 - 1.45 us) and the fp32 partials' way out and back at 4 TB/s.  (With at
+// most 8 splits, whatever they left idle, 777 tokens x 1024 x 32000 ran 128
+// blocks: dH 87 us.)
+static int dh_splits(int n_tokens, int H, int V) {
   const int tiles = ((H + BA - 1) / BA) * ((n_tokens + BT - 1) / BT);
-  if (tiles >= 4 * 256) return 1;
+  if (tiles >= 4 * kNumCu) return 1;
+  const int nk = (V + BKK - 1) / BKK;
+  const double part_us = double(n_tokens) * H * 8 / 4e6;   // one split's partial, both ways
   int best = 1;
-  double best_t = (tiles + 255) / 256;
-  for (int s = 2; s <= 8; ++s) {
-    const double t = double((tiles * s + 255) / 256) / s;
-    if (t < 0.95 * best_t) {
+  double best_t = 0;
+  for (int s = 1; s <= kMaxDhSplits && s <= nk; ++s) {
+    const double t = double((int64_t(tiles) * s + kNumCu - 1) / kNumCu) * ((nk + s - 1) / s) * 1.4 +
+                     (s > 1 ? s * part_us : 0.0);
+    if (s == 1 || t < 0.97 * best_t) {
       best_t = t;
       best = s;
     }
@@ -874,16 +907,20 @@ static int dh_splits(int n_tokens, int H) {
   return best;
 }
 
-static size_t dh_part_bytes(int T, int H) {
-  const int splits = dh_splits(T, H);
+static size_t dh_part_bytes(int T, int H, int V) {
+  const int splits = dh_splits(T, H, V);
   return splits > 1 ? align256(size_t(splits) * T * H * sizeof(float)) : 0;
 }
 
 // rows of a panel-layout matrix
 static int panel_rows(int R) { return (R + 255) / 256 * 256; }
 
-static size_t wT_bytes(int H, int V) {
-  return align256(size_t(panel_rows(H)) * vocab_pad(V) * sizeof(u16));
+// Whether the dH product reads W as it is, with transposing LDS reads, instead
+// of a transposed copy that the call first makes of it.
+static bool dh_direct(int n_tokens) { return n_tokens <= kMaxDirectDh; }
+
+static size_t wT_bytes(int n_tokens, int H, int V) {
+  return dh_direct(n_tokens) ? 0 : align256(size_t(panel_rows(H)) * vocab_pad(V) * sizeof(u16));
 }
 
 size_t kl_fwd_ws_bytes(int n, int H, int V) {
@@ -893,10 +930,10 @@ size_t kl_fwd_ws_bytes(int n, int H, int V) {
          256;
 }
 
-// G [n, Vp] | dH partials | zero row [H] | W^T [H, Vp] (G and W^T in panels)
+// G [n, Vp] | dH partials | zero row [H] | W^T [H, Vp] unless direct (G and W^T in panels)
 size_t kl_bwd_ws_bytes(int n, int H, int V) {
-  return align256(size_t(panel_rows(n)) * vocab_pad(V) * sizeof(u16)) + dh_part_bytes(n, H) +
-         align256(size_t(H) * sizeof(u16)) + wT_bytes(H, V) + 256;
+  return align256(size_t(panel_rows(n)) * vocab_pad(V) * sizeof(u16)) + dh_part_bytes(n, H, V) +
+         align256(size_t(H) * sizeof(u16)) + wT_bytes(n, H, V) + 256;
 }
 
 __global__ __launch_bounds__(256) void zero_u16_kernel(u16* p, int n) {
@@ -935,10 +972,10 @@ size_t logprob_grpo_ws_bytes(int T, int H, int V, int n_traj) {
 
 static int g_rows(int T) { return panel_rows(T); }
 
-// status | G [Tg, Vp] | dH partials | W^T [H, Vp] (G and W^T in panels)
+// status | G [Tg, Vp] | dH partials | W^T [H, Vp] unless direct (G and W^T in panels)
 size_t logprob_bwd_ws_bytes(int T, int H, int V) {
   return kStatusBytes + align256(size_t(g_rows(T)) * vocab_pad(V) * sizeof(u16)) +
-         dh_part_bytes(T, H) + wT_bytes(H, V) + 256;
+         dh_part_bytes(T, H, V) + wT_bytes(T, H, V) + 256;
 }
 
 static char* align_ptr(void* p) {
@@ -983,13 +1020,21 @@ __global__ __launch_bounds__(256) void dh_reduce_kernel(const float* part, u16* 
   if (i >= n4) return;
   const float4* p = reinterpret_cast<const float4*>(part) + i;
   float4 acc = p[0];
-  for (int s = 1; s < splits; ++s) {
-    const float4 v = p[size_t(s) * n4];
+  auto add = [&](const float4& v) {
     acc.x += v.x;
     acc.y += v.y;
     acc.z += v.z;
     acc.w += v.w;
+  };
+  int s = 1;
+  for (; s + 4 <= splits; s += 4) {   // four loads in flight
+    float4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = p[size_t(s + u) * n4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) add(v[u]);
   }
+  for (; s < splits; ++s) add(p[size_t(s) * n4]);
   uint2 w;
   w.x = pack2(acc.x, acc.y);
   w.y = pack2(acc.z, acc.w);
@@ -1000,8 +1045,8 @@ __global__ __launch_bounds__(256) void dh_reduce_kernel(const float* part, u16* 
 // the vocabulary when the output alone would leave CUs idle; `part` is the
 // fp32 partial area of the workspace (dh_part_bytes).
 static hipError_t launch_dh(LmArgs b, float* part, const char* name, hipStream_t stream) {
-  const int nk_total = b.Vp / BKK;
-  int splits = std::min(dh_splits(b.T, b.H), nk_total);
+  const int nk_total = (b.V + BKK - 1) / BKK;   // G is zero past V
+  int splits = dh_splits(b.T, b.H, b.V);
   b.nk_split = (nk_total + splits - 1) / splits;
   splits = (nk_total + b.nk_split - 1) / b.nk_split;  // no empty split
   b.k_split = splits;
@@ -1010,7 +1055,10 @@ static hipError_t launch_dh(LmArgs b, float* part, const char* name, hipStream_t
   b.nT = (b.T + BT - 1) / BT;
   {
     ProfScope p(name, stream);
-    hipLaunchKernelGGL(lm_tile_kernel<kModeDh>, gemm_grid(b), dim3(NWAVES * 64), 0, stream, b);
+    if (dh_direct(b.T))
+      hipLaunchKernelGGL(lm_tile_kernel<kModeDhW>, gemm_grid(b), dim3(NWAVES * 64), 0, stream, b);
+    else
+      hipLaunchKernelGGL(lm_tile_kernel<kModeDh>, gemm_grid(b), dim3(NWAVES * 64), 0, stream, b);
     if (splits > 1) {
       const size_t n4 = size_t(b.T) * b.H / 4;
       hipLaunchKernelGGL(dh_reduce_kernel, dim3(unsigned((n4 + 255) / 256)), dim3(256), 0, stream,
@@ -1170,14 +1218,15 @@ hipError_t launch_logprob_bwd(int T, int H, int V, const void* hidden, const voi
   char* base = align_ptr(ws) + kStatusBytes;
   u16* G = reinterpret_cast<u16*>(base);
   float* part = reinterpret_cast<float*>(base + align256(size_t(a.Tg) * a.Vp * sizeof(u16)));
-  u16* wT = reinterpret_cast<u16*>(reinterpret_cast<char*>(part) + dh_part_bytes(T, H));
+  u16* wT = reinterpret_cast<u16*>(reinterpret_cast<char*>(part) + dh_part_bytes(T, H, V));
   a.Gout = G;
   a.G = G;
   a.wT = wT;
   a.dh = static_cast<u16*>(dhidden);
   a.nA = a.Vp / BA;
   a.nT = (T + BT - 1) / BT;
-  if (hipError_t e = transpose_w(a.w, wT, V, H, "lm_wt", stream); e != hipSuccess) return e;
+  if (!dh_direct(T))
+    if (hipError_t e = transpose_w(a.w, wT, V, H, "lm_wt", stream); e != hipSuccess) return e;
   {
     ProfScope p("lm_grad", stream);
     hipLaunchKernelGGL(lm_tile_kernel<kModeGrad>, gemm_grid(a), dim3(NWAVES * 64), 0, stream, a);
@@ -1269,14 +1318,15 @@ hipError_t launch_kl_bwd(int n, int H, int V, const void* hT, int nT, const int3
   char* base = align_ptr(ws);
   u16* G = reinterpret_cast<u16*>(base);
   float* part = reinterpret_cast<float*>(base + align256(size_t(panel_rows(n)) * a.Vp * sizeof(u16)));
-  u16* zrow = reinterpret_cast<u16*>(reinterpret_cast<char*>(part) + dh_part_bytes(n, H));
+  u16* zrow = reinterpret_cast<u16*>(reinterpret_cast<char*>(part) + dh_part_bytes(n, H, V));
   u16* wT = reinterpret_cast<u16*>(reinterpret_cast<char*>(zrow) + align256(size_t(H) * sizeof(u16)));
   a.Gout = G;
   a.nA = a.Vp / BA;
   a.nT = (a.T + BT - 1) / BT;
   a.zero_row = zrow;
   if (hipError_t e = zero_row(zrow, H, stream); e != hipSuccess) return e;
-  if (hipError_t e = transpose_w(a.w, wT, V, H, "kl_wt", stream); e != hipSuccess) return e;
+  if (!dh_direct(n))
+    if (hipError_t e = transpose_w(a.w, wT, V, H, "kl_wt", stream); e != hipSuccess) return e;
   {
     ProfScope p("kl_grad", stream);
     hipLaunchKernelGGL(lm_tile_kernel<kModeKLGrad>, gemm_grid(a), dim3(NWAVES * 64), 0, stream, a);

@@ -270,6 +270,16 @@ __device__ __forceinline__ bf16x8 lds_frag(uint32_t addr) {
   return *(lds_bf16x8*)(uintptr_t)addr;
 }
 
+// An MFMA operand read across LDS rows at byte address addr and (its second
+// half) addr + hi, each one transposing read.
+__device__ __forceinline__ bf16x8 lds_frag_tr(uint32_t addr, uint32_t hi) {
+  const i16x4 l = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(uintptr_t)addr);
+  const i16x4 h = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(uintptr_t)(addr + hi));
+  typedef short i16x8 __attribute__((ext_vector_type(8)));
+  const i16x8 v = {l[0], l[1], l[2], l[3], h[0], h[1], h[2], h[3]};
+  return __builtin_bit_cast(bf16x8, v);
+}
+
 // LDS byte address of a __shared__ object
 template <typename X>
 __device__ __forceinline__ uint32_t lds_addr(X* p) {

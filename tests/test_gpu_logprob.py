@@ -52,6 +52,15 @@ def test_small_ragged(T, H, V):
     _check(*inputs, f"lp{T}x{H}x{V}")
 
 
+@pytest.mark.parametrize("T,H,V", [
+    (3072, 128, 500), (3073, 128, 500),   # the last size whose dH reads W itself, the first on W^T
+    (40, 320, 4133),    # dH in many vocabulary splits, a ragged last k slice, H past a tile
+    (5, 64, 64), (3100, 64, 65),          # one k slice; one and a ragged one
+])
+def test_dh_product_forms(T, H, V):
+    _check(*_inputs(T, H, V, 9, skip_every=11), f"dh{T}x{H}x{V}")
+
+
 def test_out_of_range_targets_are_skipped_and_counted():
     """Ids outside [-1, vocab) are never used as an index: their tokens are
     scored as tokens without loss (logp 0, ratio 1, zero dH) and counted in
