@@ -76,7 +76,7 @@ constexpr int PANEL = 256 * 64;
 __host__ __device__ inline size_t panel_index(int r, int k, int K) {
   return (size_t(r >> 8) * (K >> 6) + (k >> 6)) * PANEL + (r & 255) * 64 + (k & 63);
 }
-constexpr int FA = 8, FB = 4;                      // 16-row MFMA blocks per wave: A rows, tokens
+constexpr int FB = 4;                              // 16-row MFMA blocks per wave: tokens
 static_assert(4 * NWAVES * 1024 == SLICE_B, "two regions of two 1 KiB loads per wave");
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 int vocab_pad(int V) { return (V + BA - 1) / BA * BA; }
@@ -125,7 +125,7 @@ struct LmArgs {
 // Output tile (a0, t0) and k split of this block.  Blocks are dealt to XCDs
 // round-robin; each XCD gets a contiguous range of the rasterised tile order
 // (groups of GT token tiles x all A tiles).  False: no tile (grid tail).
-template <int GT>
+template <int GT, int TA = BA>
 __device__ __forceinline__ bool tile_of(const LmArgs& a, int n_splits, int& a0, int& t0,
                                         int& split) {
   const int n_out = a.nA * a.nT;
@@ -140,7 +140,7 @@ __device__ __forceinline__ bool tile_of(const LmArgs& a, int n_splits, int& a0, 
   const int grp = L / (GT * a.nA);
   const int rem = L % (GT * a.nA);
   const int t_in = min(GT, a.nT - grp * GT);
-  a0 = (rem / t_in) * BA;
+  a0 = (rem / t_in) * TA;
   t0 = (grp * GT + rem % t_in) * BT;
   return true;
 }
@@ -150,7 +150,7 @@ __device__ __forceinline__ bool tile_of(const LmArgs& a, int n_splits, int& a0, 
 // quarter of its tile (mma(ha, hb): half ha of its A fragments x half hb of
 // its B fragments, 256 cycles), the other loads: the fragments of its next
 // quarter from LDS (read_a / read_b of a half, from the current buffer) and
-// its share (two loads) of a region of the slice after next (issue_a /
+// its share of a region of the slice after next (issue_a /
 // issue_b(half, slice)).  A region is the part of an operand slice that the
 // waves' fragments of one half come from.  The quarters of a slice go (0,0)
 // (0,1) (1,1) (1,0); before them are read B0, B1, A1 and the next slice's A0
@@ -158,7 +158,8 @@ __device__ __forceinline__ bool tile_of(const LmArgs& a, int n_splits, int& a0, 
 // free for its next load one or two turns after it is read, and each load has
 // about 12 turns (1.5 slices) to land.  late: this wave runs one turn behind.
 // On return every load has landed and every wave is done with the LDS reads.
-template <class IA, class IB, class RA, class RB, class FL, class MM>
+// LA, LB: loads per region and wave of either operand.
+template <int LA, int LB, class IA, class IB, class RA, class RB, class FL, class MM>
 __device__ __forceinline__ void tile_pipeline(int nk, bool late, IA issue_a, IB issue_b, RA read_a,
                                               RB read_b, FL flip, MM mma) {
   auto turn = [&]() {
@@ -176,9 +177,8 @@ __device__ __forceinline__ void tile_pipeline(int nk, bool late, IA issue_a, IB 
     __builtin_amdgcn_s_setprio(0);
     turn();
   };
-  // order of the loads: A0 B0 B1 A1 of slice 0, of slice 1, ...; two loads
-  // per region and wave, so waiting for all but 12 keeps the six youngest
-  // regions in flight
+  // order of the loads: A0 B0 B1 A1 of slice 0, of slice 1, ...; each wait
+  // keeps the six regions younger than the one it waits for in flight
   auto issue_slice = [&](int kk) {
     issue_a(0, kk);
     issue_b(0, kk);
@@ -188,7 +188,7 @@ __device__ __forceinline__ void tile_pipeline(int nk, bool late, IA issue_a, IB 
   issue_slice(0);
   if (nk > 1) {
     issue_slice(1);
-    wait_vmcnt<12>();   // A0, B0 of slice 0
+    wait_vmcnt<3 * LA + 3 * LB>();   // A0, B0 of slice 0
   } else {
     wait_vmcnt<0>();
   }
@@ -226,24 +226,31 @@ __device__ __forceinline__ void tile_pipeline(int nk, bool late, IA issue_a, IB 
   using std::integral_constant;
   using T = std::true_type;
   using F = std::false_type;
-  using n12 = integral_constant<int, 12>;
-  for (int kk = 0; kk + 2 < nk; ++kk) slice(kk, T{}, F{}, n12{}, n12{}, n12{}, n12{});
+  constexpr int R = LA + LB;   // loads of half a slice
+  for (int kk = 0; kk + 2 < nk; ++kk)
+    slice(kk, T{}, F{}, integral_constant<int, 2 * R + 2 * LA>{}, integral_constant<int, 3 * R>{},
+          integral_constant<int, 2 * R + 2 * LB>{}, integral_constant<int, 3 * R>{});
   if (nk > 1)
-    slice(nk - 2, F{}, F{}, integral_constant<int, 10>{}, integral_constant<int, 8>{},
-          integral_constant<int, 6>{}, integral_constant<int, 4>{});
-  slice(nk - 1, F{}, T{}, integral_constant<int, 2>{}, integral_constant<int, 0>{},
+    slice(nk - 2, F{}, F{}, integral_constant<int, 2 * R + LA>{}, integral_constant<int, 2 * R>{},
+          integral_constant<int, R + LB>{}, integral_constant<int, R>{});
+  slice(nk - 1, F{}, T{}, integral_constant<int, LA>{}, integral_constant<int, 0>{},
         integral_constant<int, 0>{}, integral_constant<int, 0>{});
   if (!late) turn();
 }
 
-template <int MODE>
+// TA: A rows of the tile, 256 or 128 (each wave half as many rows; see
+// half_tiles).
+template <int MODE, int TA = BA>
 __global__ __launch_bounds__(NWAVES * 64, 1) void lm_tile_kernel(LmArgs a) {
   __shared__ __align__(1024) u16 smem[2 * 2 * SLICE_B / 2];   // 2 slices x 2 operands
 
+  constexpr int FA = TA / 32;      // 16-row MFMA blocks per wave along A
+  constexpr int WR = TA / 2;       // A rows per wave
+  constexpr int NQA = TA / 128;    // loads per A region and wave
   int a0, t0, split;
   constexpr bool DH = MODE == kModeDh || MODE == kModeDhW;
   constexpr int GT = DH ? GROUP_T_V : GROUP_T_H;
-  if (!tile_of<GT>(a, DH ? a.k_split : 1, a0, t0, split)) return;
+  if (!tile_of<GT, TA>(a, DH ? a.k_split : 1, a0, t0, split)) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wa = wave >> 2, wt = wave & 3;
@@ -259,7 +266,8 @@ __global__ __launch_bounds__(NWAVES * 64, 1) void lm_tile_kernel(LmArgs a) {
 
   // Slice loads.  Each operand slice is loaded in two regions of 128 rows,
   // the rows that every wave's first (region 0) and second (1) half of its
-  // fragments come from: A rows 64 of each 128, token rows 32 of each 64.
+  // fragments come from: A rows 64 of each 128 (128-row tiles: 32 of each 64,
+  // one load), token rows 32 of each 64.
   // Load q of this wave fills rows rowX(h, q) + lane / 8, whose 16-byte chunk
   // position lane % 8 holds chunk (lane % 8) ^ (row % 8).  Rows past the
   // operands are read from clamped (valid) rows; their products land in
@@ -272,7 +280,10 @@ __global__ __launch_bounds__(NWAVES * 64, 1) void lm_tile_kernel(LmArgs a) {
   constexpr bool PANELS = DH;
   constexpr bool GATHER = MODE == kModeKL || MODE == kModeKLGrad;
   constexpr uint32_t SSTEP = (PANELS ? PANEL : BKK) * 2;   // bytes from a row's k slice to the next
-  auto row_a = [&](int h, int q) { return q * 128 + h * 64 + wave * 8; };
+  auto row_a = [&](int h, int q) {
+    return TA == 256 ? q * 128 + h * 64 + wave * 8
+                     : (wave >> 2) * 64 + h * 32 + (wave & 3) * 8;
+  };
   auto row_b = [&](int h, int q) { return q * 128 + (wave >> 2) * 64 + h * 32 + (wave & 3) * 8; };
   const size_t tile_a = TRA ? size_t(0) : PANELS ? panel_index(a0, kbeg * BKK, K) : size_t(a0) * K;
   const size_t tile_b = PANELS ? panel_index(t0, kbeg * BKK, K) : size_t(t0) * K;
@@ -319,8 +330,8 @@ __global__ __launch_bounds__(NWAVES * 64, 1) void lm_tile_kernel(LmArgs a) {
       return;
     }
     const char* b = baseA + size_t(kk) * SSTEP;
-    lds_load16s(b, offA[h][0], st + row_a(h, 0) * 128);
-    lds_load16s(b, offA[h][1], st + row_a(h, 1) * 128);
+#pragma unroll
+    for (int q = 0; q < NQA; ++q) lds_load16s(b, offA[h][q], st + row_a(h, q) * 128);
   };
   auto issue_b = [&](int h, int kk) {
     const uint32_t st = lds0 + 2 * SLICE_B + (kk & 1) * SLICE_B;
@@ -336,7 +347,7 @@ __global__ __launch_bounds__(NWAVES * 64, 1) void lm_tile_kernel(LmArgs a) {
 
   // Fragments of half h: 16 consecutive rows at one chunk per read
   const int frow = lane & 15, fk = lane >> 4;
-  uint32_t pa = lds0 + (wa * 128 + frow) * 128 + ((fk ^ (frow & 7)) * 16);
+  uint32_t pa = lds0 + (wa * WR + frow) * 128 + ((fk ^ (frow & 7)) * 16);
   if (TRA) {   // lane j of a 16-lane group: row fk * 8 + j / 4 (and + 4), columns 4 (j % 4)
     const int r = fk * 8 + (frow >> 2);
     pa = lds0 + wa * 128 * 128 + r * 128 +
@@ -350,7 +361,7 @@ __global__ __launch_bounds__(NWAVES * 64, 1) void lm_tile_kernel(LmArgs a) {
 #pragma unroll
       for (int i = 0; i < FA / 2; ++i)
         fa[h][ks][i] = TRA ? lds_frag_tr((p ^ (i * 32)) + h * 8192 + ks * 32 * 128, 4 * 128)
-                           : lds_frag((p ^ (ks * 64)) + h * 8192 + i * 2048);
+                           : lds_frag((p ^ (ks * 64)) + h * (WR / 2) * 128 + i * 2048);
   };
   auto read_b = [&](int h, uint32_t p) {
 #pragma unroll
@@ -380,14 +391,14 @@ __global__ __launch_bounds__(NWAVES * 64, 1) void lm_tile_kernel(LmArgs a) {
     pa += d;
     pb += d;
   };
-  tile_pipeline(nk, wa == 1, issue_a, issue_b, [&](int h) { read_a(h, pa); },
-                [&](int h) { read_b(h, pb); }, flip, mma);
+  tile_pipeline<NQA, 2>(nk, wa == 1, issue_a, issue_b, [&](int h) { read_a(h, pa); },
+                        [&](int h) { read_b(h, pb); }, flip, mma);
 
   // acc[i][j][r]: A row rb + i*16 + r, token tb + j*16
-  const int rb = a0 + wa * 128 + (lane >> 4) * 4;
+  const int rb = a0 + wa * WR + (lane >> 4) * 4;
   const int tb = t0 + wt * 64 + (lane & 15);
-  const bool full_v = a0 + BA <= a.V;  // block-uniform: no vocabulary padding in this tile
-  const int chunk = (a0 + wa * 128) / 128;
+  const bool full_v = a0 + TA <= a.V;  // block-uniform: no vocabulary padding in this tile
+  const int chunk = (a0 + wa * WR) / WR;
   if (MODE == kModeLogits) {
 #pragma unroll
     for (int j = 0; j < FB; ++j) {
@@ -453,7 +464,7 @@ __global__ __launch_bounds__(NWAVES * 64, 1) void lm_tile_kernel(LmArgs a) {
     __syncthreads();
     uint4* gt = reinterpret_cast<uint4*>(a.Gout + panel_index(t0, a0, a.Vp));
 #pragma unroll 4
-    for (int k = tid; k < 128 * 1024 / 16; k += NWAVES * 64) {
+    for (int k = tid; k < TA * BT * 2 / 16; k += NWAVES * 64) {
       const int q = k >> 11, r = (k >> 3) & 255, c16 = k & 7;
       gt[k] = *reinterpret_cast<const uint4*>(sg + (q << 15) + (r << 7) + ((c16 ^ (r & 7)) << 4));
     }
@@ -654,7 +665,7 @@ __global__ __launch_bounds__(NWAVES * 64, 1) void lm_dw_kernel(LmArgs a) {
       for (int i = 0; i < 2; ++i)
         acc[ha * 2 + i][hb] = mfma32(fa[ha][ks][i], fb[hb][ks], acc[ha * 2 + i][hb]);
   };
-  tile_pipeline(nk, wa == 1, issue_a, issue_b, read_a, read_b, flip, mma);
+  tile_pipeline<2, 2>(nk, wa == 1, issue_a, issue_b, read_a, read_b, flip, mma);
 
   // acc[i][j][r]: vocabulary row a0 + wa*128 + i*32 + (r/4)*8 + g*4 + r%4,
   //               hidden column t0 + j*128 + wt*32 + c
@@ -912,6 +923,23 @@ static size_t dh_part_bytes(int T, int H, int V) {
   return splits > 1 ? align256(size_t(splits) * T * H * sizeof(float)) : 0;
 }
 
+// Whether the products over the hidden dimension take 128-row vocabulary
+// tiles instead of 256: only when twice as many tiles still run at once.  A
+// tile of half the rows takes 0.73 of the time (it has half the bytes of W in
+// flight): 100 tokens x 1024 x 32000 (125 tiles), training step: 141 -> 130
+// us, 100 leaves: 94 -> 84 us; but 201 tokens x 3584 x 152064 (594 tiles, 3
+// rounds of resident blocks against 5 half ones), scoring: 273 -> 320 us.
+static bool half_tiles(int n_tokens, int V) {
+  return 2 * int64_t(vocab_pad(V) / BA) * ((n_tokens + BT - 1) / BT) <= kNumCu;
+}
+// vocabulary tiles (each holds some row < V: a tile clamps its rows to V - 1)
+static int tiles_a(int n_tokens, int V) {
+  const int rows = half_tiles(n_tokens, V) ? 128 : BA;
+  return (V + rows - 1) / rows;
+}
+// per-token partials of the logits and KL passes: one per tile and wave row
+static int n_chunks_of(int n_tokens, int V) { return 2 * tiles_a(n_tokens, V); }
+
 // rows of a panel-layout matrix
 static int panel_rows(int R) { return (R + 255) / 256 * 256; }
 
@@ -924,7 +952,7 @@ static size_t wT_bytes(int n_tokens, int H, int V) {
 }
 
 size_t kl_fwd_ws_bytes(int n, int H, int V) {
-  const int n_chunks = vocab_pad(V) / 128;
+  const int n_chunks = n_chunks_of(2 * n, V);
   return align256(size_t(n) * n_chunks * sizeof(float4)) +
          align256(size_t(n) * n_chunks * sizeof(float2)) + align256(size_t(H) * sizeof(u16)) +
          256;
@@ -955,7 +983,7 @@ constexpr size_t kStatusBytes = 256;
 // status | per-(token, chunk) (max, sum)
 size_t logprob_fwd_ws_bytes(int T, int H, int V) {
   (void)H;
-  const int n_chunks = vocab_pad(V) / 128;
+  const int n_chunks = n_chunks_of(T, V);
   return kStatusBytes + align256(size_t(T) * n_chunks * sizeof(float2)) + 256;
 }
 
@@ -1002,6 +1030,14 @@ static dim3 gemm_grid(const LmArgs& a) {
   const int splits = a.k_split > 1 ? a.k_split : 1;
   const int per_xcd = (a.nA * a.nT * splits + kNumXcd - 1) / kNumXcd;
   return dim3(per_xcd * kNumXcd);
+}
+
+template <int MODE>
+static void launch_tile(const LmArgs& a, hipStream_t stream) {
+  if (half_tiles(a.T, a.V))
+    hipLaunchKernelGGL((lm_tile_kernel<MODE, 128>), gemm_grid(a), dim3(NWAVES * 64), 0, stream, a);
+  else
+    hipLaunchKernelGGL((lm_tile_kernel<MODE, 256>), gemm_grid(a), dim3(NWAVES * 64), 0, stream, a);
 }
 
 static hipError_t transpose_w(const u16* w, u16* wT, int V, int H, const char* name,
@@ -1097,7 +1133,7 @@ static hipError_t logprob_fwd_common(LmArgs& a, void* ws, const CombineOut& o, b
                                      const uint8_t* grpo_mask, hipStream_t stream) {
   a.bad_targets = clear_status(ws, stream);
   a.part = reinterpret_cast<float2*>(align_ptr(ws) + kStatusBytes);
-  a.nA = a.Vp / BA;
+  a.nA = tiles_a(a.T, a.V);
   a.nT = (a.T + BT - 1) / BT;
   if (grpo) {
     const int blocks = std::max((a.T + 1023) / 1024, (o.n_traj + 255) / 256);
@@ -1109,7 +1145,7 @@ static hipError_t logprob_fwd_common(LmArgs& a, void* ws, const CombineOut& o, b
   if (a.T == 0) return hipGetLastError();
   {
     ProfScope p("lm_logits", stream);
-    hipLaunchKernelGGL(lm_tile_kernel<kModeLogits>, gemm_grid(a), dim3(NWAVES * 64), 0, stream, a);
+    launch_tile<kModeLogits>(a, stream);
   }
   {
     ProfScope p("lm_combine", stream);
@@ -1133,7 +1169,7 @@ static LmArgs fwd_args(int T, int H, int V, const void* hidden, const void* weig
   a.H = H;
   a.V = V;
   a.Vp = vocab_pad(V);
-  a.n_chunks = a.Vp / 128;
+  a.n_chunks = n_chunks_of(T, V);
   return a;
 }
 
@@ -1223,13 +1259,13 @@ hipError_t launch_logprob_bwd(int T, int H, int V, const void* hidden, const voi
   a.G = G;
   a.wT = wT;
   a.dh = static_cast<u16*>(dhidden);
-  a.nA = a.Vp / BA;
+  a.nA = tiles_a(a.T, a.V);
   a.nT = (T + BT - 1) / BT;
   if (!dh_direct(T))
     if (hipError_t e = transpose_w(a.w, wT, V, H, "lm_wt", stream); e != hipSuccess) return e;
   {
     ProfScope p("lm_grad", stream);
-    hipLaunchKernelGGL(lm_tile_kernel<kModeGrad>, gemm_grid(a), dim3(NWAVES * 64), 0, stream, a);
+    launch_tile<kModeGrad>(a, stream);
   }
   {
     ProfScope p("lm_target", stream);
@@ -1273,7 +1309,7 @@ hipError_t launch_kl_fwd(int n, int H, int V, const void* hT, int nT, const int3
   a.H = H;
   a.V = V;
   a.Vp = vocab_pad(V);
-  a.n_chunks = a.Vp / 128;
+  a.n_chunks = n_chunks_of(a.T, V);
   char* base = align_ptr(ws);
   a.partT = reinterpret_cast<float4*>(base);
   a.partS = reinterpret_cast<float2*>(base + align256(size_t(n) * a.n_chunks * sizeof(float4)));
@@ -1281,11 +1317,11 @@ hipError_t launch_kl_fwd(int n, int H, int V, const void* hT, int nT, const int3
                                      align256(size_t(n) * a.n_chunks * sizeof(float2)));
   a.zero_row = zrow;
   if (hipError_t e = zero_row(zrow, H, stream); e != hipSuccess) return e;
-  a.nA = a.Vp / BA;
+  a.nA = tiles_a(a.T, a.V);
   a.nT = (a.T + BT - 1) / BT;
   {
     ProfScope p("kl_logits", stream);
-    hipLaunchKernelGGL(lm_tile_kernel<kModeKL>, gemm_grid(a), dim3(NWAVES * 64), 0, stream, a);
+    launch_tile<kModeKL>(a, stream);
   }
   {
     ProfScope p("kl_combine", stream);
@@ -1321,7 +1357,7 @@ hipError_t launch_kl_bwd(int n, int H, int V, const void* hT, int nT, const int3
   u16* zrow = reinterpret_cast<u16*>(reinterpret_cast<char*>(part) + dh_part_bytes(n, H, V));
   u16* wT = reinterpret_cast<u16*>(reinterpret_cast<char*>(zrow) + align256(size_t(H) * sizeof(u16)));
   a.Gout = G;
-  a.nA = a.Vp / BA;
+  a.nA = tiles_a(a.T, a.V);
   a.nT = (a.T + BT - 1) / BT;
   a.zero_row = zrow;
   if (hipError_t e = zero_row(zrow, H, stream); e != hipSuccess) return e;
@@ -1329,7 +1365,7 @@ hipError_t launch_kl_bwd(int n, int H, int V, const void* hT, int nT, const int3
     if (hipError_t e = transpose_w(a.w, wT, V, H, "kl_wt", stream); e != hipSuccess) return e;
   {
     ProfScope p("kl_grad", stream);
-    hipLaunchKernelGGL(lm_tile_kernel<kModeKLGrad>, gemm_grid(a), dim3(NWAVES * 64), 0, stream, a);
+    launch_tile<kModeKLGrad>(a, stream);
   }
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   // dh = G W over the leaves

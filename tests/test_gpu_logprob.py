@@ -56,6 +56,9 @@ def test_small_ragged(T, H, V):
     (3072, 128, 500), (3073, 128, 500),   # the last size whose dH reads W itself, the first on W^T
     (40, 320, 4133),    # dH in many vocabulary splits, a ragged last k slice, H past a tile
     (5, 64, 64), (3100, 64, 65),          # one k slice; one and a ragged one
+    (256, 64, 32641), (256, 64, 32769),   # the most 128-row vocabulary tiles, the last of one
+                                          # row; 256-row tiles, likewise
+    (257, 128, 8200), (700, 64, 11009),   # two and three token tiles of either
 ])
 def test_dh_product_forms(T, H, V):
     _check(*_inputs(T, H, V, 9, skip_every=11), f"dh{T}x{H}x{V}")
