@@ -244,6 +244,10 @@ template <int MODE, int TA = BA>
 __global__ __launch_bounds__(NWAVES * 64, 1) void lm_tile_kernel(LmArgs a) {
   __shared__ __align__(1024) u16 smem[2 * 2 * SLICE_B / 2];   // 2 slices x 2 operands
 
+  // the call's status block (256 bytes), for the passes after this one
+  if ((MODE == kModeLogits || MODE == kModeGrad) && blockIdx.x == 0 && threadIdx.x < 64)
+    a.bad_targets[threadIdx.x] = 0;
+
   constexpr int FA = TA / 32;      // 16-row MFMA blocks per wave along A
   constexpr int WR = TA / 2;       // A rows per wave
   constexpr int NQA = TA / 128;    // loads per A region and wave
@@ -810,12 +814,29 @@ __global__ __launch_bounds__(256) void lm_combine_kernel(LmArgs a, CombineOut o)
     else if (lane == 0 && y != -1)
       atomicAdd(a.bad_targets, 1);
     const float2* p = a.part + size_t(t) * a.n_chunks;
-    float m = -INFINITY;
-    for (int i = lane; i < a.n_chunks; i += 64) m = fmaxf(m, p[i].x);
+    // the lane's partials, read once, kMerge loads in flight
+    constexpr int kMerge = 8;
+    float m = -INFINITY, s = 0.f;
+    for (int i0 = lane; i0 < a.n_chunks; i0 += 64 * kMerge) {
+      float2 x[kMerge];
+      float mx = m;
+#pragma unroll
+      for (int u = 0; u < kMerge; ++u) {
+        const int i = i0 + 64 * u;
+        x[u] = i < a.n_chunks ? p[i] : make_float2(-INFINITY, 0.f);
+      }
+#pragma unroll
+      for (int u = 0; u < kMerge; ++u) mx = fmaxf(mx, x[u].x);
+      const float mu = mx == -INFINITY ? 0.f : mx;   // chunks of padding only
+      s *= fast_exp2(m - mu);
+#pragma unroll
+      for (int u = 0; u < kMerge; ++u) s += x[u].y * fast_exp2(x[u].x - mu);
+      m = mx;
+    }
+    const float m_lane = m;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-    float s = 0.f;
-    for (int i = lane; i < a.n_chunks; i += 64) s += p[i].y * fast_exp2(p[i].x - m);
+    s *= fast_exp2(m_lane - m);   // a lane without partials: 0 (and a NaN stays one)
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
     if (lane == 0) {
@@ -1014,14 +1035,6 @@ __global__ __launch_bounds__(64) void clear_status_kernel(int* status) {
   status[threadIdx.x] = 0;   // the whole 256-byte block
 }
 
-// The status block of a log-prob workspace, cleared on the stream (a kernel,
-// not a memset, so that the call can be captured in a graph).
-static int* clear_status(void* ws, hipStream_t stream) {
-  int* st = reinterpret_cast<int*>(align_ptr(ws));
-  hipLaunchKernelGGL(clear_status_kernel, dim3(1), dim3(64), 0, stream, st);
-  return st;
-}
-
 int* logprob_status_word(const void* ws) {
   return reinterpret_cast<int*>(align_ptr(const_cast<void*>(ws)));
 }
@@ -1131,10 +1144,18 @@ __global__ __launch_bounds__(256) void grpo_prep_kernel(const uint8_t* mask, int
 
 static hipError_t logprob_fwd_common(LmArgs& a, void* ws, const CombineOut& o, bool grpo,
                                      const uint8_t* grpo_mask, hipStream_t stream) {
-  a.bad_targets = clear_status(ws, stream);
+  a.bad_targets = logprob_status_word(ws);
   a.part = reinterpret_cast<float2*>(align_ptr(ws) + kStatusBytes);
   a.nA = tiles_a(a.T, a.V);
   a.nT = (a.T + BT - 1) / BT;
+  // the status block is cleared by the logits pass (by a kernel, not a
+  // memset, so that the call can be captured in a graph)
+  if (a.T > 0) {
+    ProfScope p("lm_logits", stream);
+    launch_tile<kModeLogits>(a, stream);
+  } else {
+    hipLaunchKernelGGL(clear_status_kernel, dim3(1), dim3(64), 0, stream, a.bad_targets);
+  }
   if (grpo) {
     const int blocks = std::max((a.T + 1023) / 1024, (o.n_traj + 255) / 256);
     ProfScope p("grpo_prep", stream);
@@ -1143,10 +1164,6 @@ static hipError_t logprob_fwd_common(LmArgs& a, void* ws, const CombineOut& o, b
                        const_cast<float*>(o.adv));
   }
   if (a.T == 0) return hipGetLastError();
-  {
-    ProfScope p("lm_logits", stream);
-    launch_tile<kModeLogits>(a, stream);
-  }
   {
     ProfScope p("lm_combine", stream);
     if (grpo)
@@ -1250,7 +1267,7 @@ hipError_t launch_logprob_bwd(int T, int H, int V, const void* hidden, const voi
   a.V = V;
   a.Vp = vocab_pad(V);
   a.Tg = g_rows(T);
-  a.bad_targets = clear_status(ws, stream);
+  a.bad_targets = logprob_status_word(ws);   // cleared by the G pass
   char* base = align_ptr(ws) + kStatusBytes;
   u16* G = reinterpret_cast<u16*>(base);
   float* part = reinterpret_cast<float*>(base + align256(size_t(a.Tg) * a.Vp * sizeof(u16)));
