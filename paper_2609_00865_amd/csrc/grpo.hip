@@ -3,15 +3,21 @@
 // inside the LM head's combine pass: mv_token_logprob_grpo; both use the
 // per-token arithmetic of mv_grpo_dev.h).
 //
-// Four small launches (all HBM-trivial next to the LM-head GEMMs):
-//   1. group-normalised advantage per trajectory;
-//   2. per token: the trajectory by binary search of the packed offsets, the
-//      ratio, the clipped surrogate and its gradient, the k3 reference KL and
-//      the drift |logp - logp_old|; unnormalised gradient out, per-block
-//      partial sums to the workspace (fixed-order tree in LDS);
-//   3. one block sums the partials in block order (fp64) into the statistics;
-//   4. the gradient is scaled by 1 / (number of loss tokens).
+// Two small launches (HBM-trivial next to the LM-head GEMMs; bound by launches
+// and their latency: as four, advantage / token / statistics / scale, 64 x 512
+// tokens took 23.4 us a call):
+//   1. per token: the trajectory by binary search of the packed offsets, its
+//      group-normalised advantage (once per trajectory and block), the ratio,
+//      the clipped surrogate and its gradient, the k3 reference KL and the
+//      drift |logp - logp_old|; unnormalised gradient out, per-block partial
+//      sums to the workspace (fixed-order tree in LDS); the advantages;
+//   2. the gradient scaled by 1 / (number of loss tokens), which every block
+//      sums for itself from the partials (whole numbers: exact in any order);
+//      the last block sums all partials in block order (fp64) into the
+//      statistics.
 // Every reduction has a fixed order, so results are bitwise reproducible.
+#include <algorithm>
+
 #include "mv_grpo_dev.h"
 
 namespace mv {
@@ -38,24 +44,28 @@ struct GrpoArgs {
   float eps_lo, eps_hi, beta, adv_eps;
 };
 
-__global__ __launch_bounds__(256) void grpo_adv_kernel(GrpoArgs a) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= a.n_traj) return;
-  a.adv[i] = grpo_advantage(a.reward, a.G, i, a.adv_eps);
-}
-
-__global__ __launch_bounds__(kTok) void grpo_token_kernel(GrpoArgs a) {
+__global__ __launch_bounds__(kTok) void grpo_token_kernel(GrpoArgs a, int n_blocks) {
   __shared__ float red[kNP][kTok];
-  const int t = blockIdx.x * kTok + threadIdx.x;
+  __shared__ float adv_of[kTok];   // at a trajectory's first token in the block
+  const int b0 = blockIdx.x * kTok, t = b0 + threadIdx.x;
+  for (int i = t; i < a.n_traj; i += gridDim.x * kTok)
+    a.adv[i] = grpo_advantage(a.reward, a.G, i, a.adv_eps);
+  if (blockIdx.x >= n_blocks) return;   // no tokens at all
   float v[kNP] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  int first = 0;
   if (t < a.T) {
     const int tr = grpo_traj_of(a.traj_ptr, a.n_traj, t);
+    first = min(max(a.traj_ptr[tr] - b0, 0), kTok - 1);
+    if (first == int(threadIdx.x)) adv_of[first] = grpo_advantage(a.reward, a.G, tr, a.adv_eps);
+  }
+  __syncthreads();
+  if (t < a.T) {
     const bool on = a.mask == nullptr || a.mask[t] != 0;
     float g = 0.f;
     if (on)
       g = grpo_token_terms(a.logp[t], a.logp_old[t],
-                           a.logp_ref != nullptr ? a.logp_ref + t : nullptr, a.adv[tr], a.eps_lo,
-                           a.eps_hi, a.beta, v);
+                           a.logp_ref != nullptr ? a.logp_ref + t : nullptr, adv_of[first],
+                           a.eps_lo, a.eps_hi, a.beta, v);
     a.dlogp[t] = g;
   }
 #pragma unroll
@@ -68,16 +78,15 @@ __global__ __launch_bounds__(kTok) void grpo_token_kernel(GrpoArgs a) {
     }
     __syncthreads();
   }
-  if (threadIdx.x < kNP) a.part[size_t(threadIdx.x) * gridDim.x + blockIdx.x] = red[threadIdx.x][0];
+  if (threadIdx.x < kNP) a.part[size_t(threadIdx.x) * n_blocks + blockIdx.x] = red[threadIdx.x][0];
 }
 
 // One block: the per-block partials (counter-major: counter k of block b at
 // part[k * stride + b]) summed in fp64, thread-strided (16-byte loads where
 // the rows allow them) then a fixed tree, into the statistics.
 constexpr int kFinish = 512;
-__global__ __launch_bounds__(kFinish) void grpo_finish_kernel(GrpoArgs a, int n_blocks,
-                                                              int stride) {
-  __shared__ double red[kNP + 1][kFinish];
+__device__ __forceinline__ void grpo_finish(const GrpoArgs& a, int n_blocks, int stride,
+                                            double (&red)[kNP + 1][kFinish]) {
   double v[kNP + 1] = {0, 0, 0, 0, 0, 0, 0, 0};
   const bool vec = (stride & 3) == 0 && (reinterpret_cast<uintptr_t>(a.part) & 15) == 0;
   const int n4 = vec ? n_blocks / 4 : 0;
@@ -117,11 +126,27 @@ __global__ __launch_bounds__(kFinish) void grpo_finish_kernel(GrpoArgs a, int n_
   a.stats[7] = a.n_traj > 0 ? float(red[kNP][0] / a.n_traj) : 0.f;  // mean |advantage|
 }
 
-__global__ __launch_bounds__(256) void grpo_scale_kernel(GrpoArgs a) {
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  if (t >= a.T) return;
-  const float n = a.stats[6];
-  a.dlogp[t] = n > 0.f ? a.dlogp[t] / n : 0.f;
+__global__ __launch_bounds__(kFinish) void grpo_finish_kernel(GrpoArgs a, int n_blocks,
+                                                              int stride) {
+  __shared__ double red[kNP + 1][kFinish];
+  grpo_finish(a, n_blocks, stride, red);
+}
+
+// The last block: the statistics; the others: kFinish tokens' gradients.
+__global__ __launch_bounds__(kFinish) void grpo_scale_kernel(GrpoArgs a, int n_blocks) {
+  __shared__ double red[kNP + 1][kFinish];
+  if (blockIdx.x + 1 == gridDim.x) {
+    grpo_finish(a, n_blocks, n_blocks, red);
+    return;
+  }
+  const int t = blockIdx.x * kFinish + threadIdx.x;
+  const float g = t < a.T ? a.dlogp[t] : 0.f;
+  double c = 0.0;   // loss tokens, of the blocks this lane of the wave takes
+  for (int b = threadIdx.x & 63; b < n_blocks; b += 64) c += a.part[b];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off);
+  const float n = float(c);
+  if (t < a.T) a.dlogp[t] = n > 0.f ? g / n : 0.f;
 }
 
 size_t grpo_ws_bytes(int T, int n_traj) {
@@ -157,13 +182,10 @@ hipError_t launch_grpo(int T, int n_traj, int G, float eps_lo, float eps_hi, flo
   a.beta = logp_ref != nullptr ? beta : 0.f;
   a.adv_eps = adv_eps;
   ProfScope prof("grpo", stream);
-  hipLaunchKernelGGL(grpo_adv_kernel, dim3((n_traj + 255) / 256), dim3(256), 0, stream, a);
-  if (T > 0)
-    hipLaunchKernelGGL(grpo_token_kernel, dim3(n_blocks), dim3(kTok), 0, stream, a);
-  hipLaunchKernelGGL(grpo_finish_kernel, dim3(1), dim3(kFinish), 0, stream, a, n_blocks,
+  hipLaunchKernelGGL(grpo_token_kernel, dim3(std::max(1, n_blocks)), dim3(kTok), 0, stream, a,
                      n_blocks);
-  if (T > 0)
-    hipLaunchKernelGGL(grpo_scale_kernel, dim3((T + 255) / 256), dim3(256), 0, stream, a);
+  hipLaunchKernelGGL(grpo_scale_kernel, dim3((T + kFinish - 1) / kFinish + 1), dim3(kFinish), 0,
+                     stream, a, n_blocks);
   return hipGetLastError();
 }
 
