@@ -11,8 +11,10 @@
 //  2. dK/dV: per 128-key tile and KV head, over the contiguous row range that
 //     sees some key of the tile, for every query head of the GQA group:
 //     S = Q K^T, dV^T += dO^T P, dP = dO V^T, dK^T += Q^T dS.
-//     Long ranges are cut into items that write fp32 partial tiles; a reduce
-//     pass sums them in a fixed order (deterministic, no atomics).
+//     Long ranges are cut into items, or the whole pass into one share of
+//     equal cost per CU where the items are too few to fill the chip; what is
+//     part of a tile goes to fp32 partial tiles, and a reduce pass sums them in
+//     a fixed order (deterministic, no atomics).
 // All stores write whole 16-byte or 8-byte runs of a row.
 #include <mutex>
 #include <type_traits>
