@@ -827,10 +827,11 @@ static SharePlan share_plan(const mv_view_mask& m, int G, int Hkv, int workers) 
 }
 
 // D [Hq, T] | LSE * log2 e [Hq, T] | fp32 partials [n_slots, Hkv, 2, 128, D]
-// or [2 workers, 2, 128, D]
+// or [2 workers, 2, 128, D]; room for either, so that what the static scratch
+// refuses does not depend on the choice
 size_t attn_bwd_ws_bytes(const mv_view_mask& m, int Hq, int Hkv, int D) {
-  const int n = bwd_workers(m, Hq, Hkv, D);
-  return bwd_ws_bytes(m, Hq, D, n ? 2 * size_t(n) : size_t(m.n_slots) * Hkv);
+  const size_t n = bwd_workers(m, Hq, Hkv, D);
+  return bwd_ws_bytes(m, Hq, D, std::max(2 * n, size_t(m.n_slots) * Hkv));
 }
 
 hipError_t launch_attn_bwd(const mv_view_mask& m, int Hq, int Hkv, int D, float scale,

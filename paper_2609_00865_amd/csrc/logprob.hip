@@ -56,6 +56,7 @@ constexpr int BA = 256, BT = 256, BKK = 64;
 // it runs 13% faster (4001 tokens: 3.09 against 3.53 ms; 1384 leaves: 1.12
 // against 1.30 ms; 32768 tokens: 22.7 against 25.9 ms).
 constexpr int kMaxDirectDh = 3072;
+constexpr int kMaxDhBlocks = 2048;         // output tiles times splits
 constexpr int kMaxDhSplits = 32;           // fp32 partials of a dH product split over the vocabulary
 constexpr int NWAVES = 8;                  // waves per tile (2 x 4 grid)
 // token tiles per raster group: 8 x 4 A tiles run side by side on an XCD
@@ -923,12 +924,12 @@ __global__ __launch_bounds__(256) void kl_combine_kernel(LmArgs a, float* kl, fl
 // blocks: dH 87 us.)
 static int dh_splits(int n_tokens, int H, int V) {
   const int tiles = ((H + BA - 1) / BA) * ((n_tokens + BT - 1) / BT);
-  if (tiles >= 4 * kNumCu) return 1;
+  if (tiles >= 4 * kNumCu || tiles == 0) return 1;
   const int nk = (V + BKK - 1) / BKK;
   const double part_us = double(n_tokens) * H * 8 / 4e6;   // one split's partial, both ways
   int best = 1;
   double best_t = 0;
-  for (int s = 1; s <= kMaxDhSplits && s <= nk; ++s) {
+  for (int s = 1; s <= kMaxDhSplits && s <= nk && tiles * s <= kMaxDhBlocks; ++s) {
     const double t = double((int64_t(tiles) * s + kNumCu - 1) / kNumCu) * ((nk + s - 1) / s) * 1.4 +
                      (s > 1 ? s * part_us : 0.0);
     if (s == 1 || t < 0.97 * best_t) {
@@ -939,9 +940,12 @@ static int dh_splits(int n_tokens, int H, int V) {
   return best;
 }
 
-static size_t dh_part_bytes(int T, int H, int V) {
-  const int splits = dh_splits(T, H, V);
-  return splits > 1 ? align256(size_t(splits) * T * H * sizeof(float)) : 0;
+// Room for the partials: an upper bound of splits * T * H floats that never
+// shrinks as T grows (splits <= kMaxDhSplits, tiles * splits <= kMaxDhBlocks),
+// so that a workspace sized for some tokens serves any fewer.
+static size_t dh_part_bytes(int T, int H) {
+  return align256(std::min(size_t(kMaxDhSplits) * T * H, size_t(kMaxDhBlocks) * BA * BT) *
+                  sizeof(float));
 }
 
 // Whether the products over the hidden dimension take 128-row vocabulary
@@ -958,6 +962,8 @@ static int tiles_a(int n_tokens, int V) {
   const int rows = half_tiles(n_tokens, V) ? 128 : BA;
   return (V + rows - 1) / rows;
 }
+// partials of the logits pass at most where its tiles are 128 rows (KL: half)
+constexpr size_t kHalfPartials = size_t(BT) * 2 * kNumCu;
 // per-token partials of the logits and KL passes: one per tile and wave row
 static int n_chunks_of(int n_tokens, int V) { return 2 * tiles_a(n_tokens, V); }
 
@@ -973,15 +979,14 @@ static size_t wT_bytes(int n_tokens, int H, int V) {
 }
 
 size_t kl_fwd_ws_bytes(int n, int H, int V) {
-  const int n_chunks = n_chunks_of(2 * n, V);
-  return align256(size_t(n) * n_chunks * sizeof(float4)) +
-         align256(size_t(n) * n_chunks * sizeof(float2)) + align256(size_t(H) * sizeof(u16)) +
-         256;
+  const size_t np = std::max(size_t(n) * n_chunks_of(2 * n, V), kHalfPartials / 2);
+  return align256(np * sizeof(float4)) + align256(np * sizeof(float2)) +
+         align256(size_t(H) * sizeof(u16)) + 256;
 }
 
 // G [n, Vp] | dH partials | zero row [H] | W^T [H, Vp] unless direct (G and W^T in panels)
 size_t kl_bwd_ws_bytes(int n, int H, int V) {
-  return align256(size_t(panel_rows(n)) * vocab_pad(V) * sizeof(u16)) + dh_part_bytes(n, H, V) +
+  return align256(size_t(panel_rows(n)) * vocab_pad(V) * sizeof(u16)) + dh_part_bytes(n, H) +
          align256(size_t(H) * sizeof(u16)) + wT_bytes(n, H, V) + 256;
 }
 
@@ -1004,8 +1009,10 @@ constexpr size_t kStatusBytes = 256;
 // status | per-(token, chunk) (max, sum)
 size_t logprob_fwd_ws_bytes(int T, int H, int V) {
   (void)H;
-  const int n_chunks = n_chunks_of(T, V);
-  return kStatusBytes + align256(size_t(T) * n_chunks * sizeof(float2)) + 256;
+  // (at least what any 128-row tiling takes: a workspace sized for some tokens
+  // serves any fewer)
+  return kStatusBytes +
+         align256(std::max(size_t(T) * n_chunks_of(T, V), kHalfPartials) * sizeof(float2)) + 256;
 }
 
 // the forward's workspace | GRPO per-block partials (4 tokens a block) |
@@ -1024,7 +1031,7 @@ static int g_rows(int T) { return panel_rows(T); }
 // status | G [Tg, Vp] | dH partials | W^T [H, Vp] unless direct (G and W^T in panels)
 size_t logprob_bwd_ws_bytes(int T, int H, int V) {
   return kStatusBytes + align256(size_t(g_rows(T)) * vocab_pad(V) * sizeof(u16)) +
-         dh_part_bytes(T, H, V) + wT_bytes(T, H, V) + 256;
+         dh_part_bytes(T, H) + wT_bytes(T, H, V) + 256;
 }
 
 static char* align_ptr(void* p) {
@@ -1271,7 +1278,7 @@ hipError_t launch_logprob_bwd(int T, int H, int V, const void* hidden, const voi
   char* base = align_ptr(ws) + kStatusBytes;
   u16* G = reinterpret_cast<u16*>(base);
   float* part = reinterpret_cast<float*>(base + align256(size_t(a.Tg) * a.Vp * sizeof(u16)));
-  u16* wT = reinterpret_cast<u16*>(reinterpret_cast<char*>(part) + dh_part_bytes(T, H, V));
+  u16* wT = reinterpret_cast<u16*>(reinterpret_cast<char*>(part) + dh_part_bytes(T, H));
   a.Gout = G;
   a.G = G;
   a.wT = wT;
@@ -1371,7 +1378,7 @@ hipError_t launch_kl_bwd(int n, int H, int V, const void* hT, int nT, const int3
   char* base = align_ptr(ws);
   u16* G = reinterpret_cast<u16*>(base);
   float* part = reinterpret_cast<float*>(base + align256(size_t(panel_rows(n)) * a.Vp * sizeof(u16)));
-  u16* zrow = reinterpret_cast<u16*>(reinterpret_cast<char*>(part) + dh_part_bytes(n, H, V));
+  u16* zrow = reinterpret_cast<u16*>(reinterpret_cast<char*>(part) + dh_part_bytes(n, H));
   u16* wT = reinterpret_cast<u16*>(reinterpret_cast<char*>(zrow) + align256(size_t(H) * sizeof(u16)));
   a.Gout = G;
   a.nA = tiles_a(a.T, a.V);
