@@ -82,6 +82,36 @@ def test_bench_shape():
     _check(*_run([512] * 64, 16, 5), "grpo-64x512")
 
 
+def _call_us(T, n_traj):
+    """Time of one loss call among others, the least of five runs of ten."""
+    ptr = torch.linspace(0, T, n_traj + 1, dtype=torch.float64).round().to(torch.int32).cuda()
+    r, lp = torch.ones(n_traj, device="cuda"), torch.zeros(T, device="cuda")
+    best = float("inf")
+    for _ in range(5):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        for _ in range(10):
+            mv.grpo_loss(ptr, r, lp, lp, lp, group_size=8, beta=0.04)
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) * 100)
+    print(f"[gpu] grpo T={T} n_traj={n_traj}: {best:.1f} us", flush=True)
+    return best
+
+
+def test_tokens_past_the_scale_blocks():
+    """More tokens than the second pass has threads (512 blocks of 512), the
+    last stride a ragged one."""
+    _check(*_run([100000, 0, 163001, 40000], 2, 6), "grpo-303001")
+
+
+def test_time_grows_with_the_tokens():
+    """Four times the tokens cost at most about four times as much (measured
+    3.5; 12 where every wave read all blocks' counts)."""
+    _call_us(1 << 20, 64)
+    assert _call_us(1 << 24, 64) < 8 * _call_us(1 << 22, 64)
+
+
 # ---------------------------------------------------------------------------
 # The loss fused into the LM head's combine pass (mv_token_logprob_grpo)
 # ---------------------------------------------------------------------------
