@@ -50,9 +50,8 @@ __global__ __launch_bounds__(kTok) void grpo_token_kernel(GrpoArgs a, int n_bloc
   __shared__ float red[kNP][kTok];
   __shared__ float adv_of[kTok];   // at a trajectory's first token in the block
   const int b0 = blockIdx.x * kTok, t = b0 + threadIdx.x;
-  for (int i = t; i < a.n_traj; i += gridDim.x * kTok)
-    a.adv[i] = grpo_advantage(a.reward, a.G, i, a.adv_eps);
-  if (blockIdx.x >= n_blocks) return;   // no tokens at all
+  if (t < a.n_traj) a.adv[t] = grpo_advantage(a.reward, a.G, t, a.adv_eps);
+  if (blockIdx.x >= n_blocks) return;   // a block of advantages only
   float v[kNP] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   int first = 0;
   bool on = false;
@@ -199,8 +198,12 @@ hipError_t launch_grpo(int T, int n_traj, int G, float eps_lo, float eps_hi, flo
   a.beta = logp_ref != nullptr ? beta : 0.f;
   a.adv_eps = adv_eps;
   ProfScope prof("grpo", stream);
-  hipLaunchKernelGGL(grpo_token_kernel, dim3(std::max(1, n_blocks)), dim3(kTok), 0, stream, a,
-                     n_blocks);
+  // a block per kTok tokens, and as many as give every trajectory a thread
+  // (256 tokens of 100000 trajectories, most of them empty, with the token
+  // blocks alone: 545 us a call instead of 66)
+  const int adv_blocks = (n_traj + kTok - 1) / kTok;
+  hipLaunchKernelGGL(grpo_token_kernel, dim3(std::max(adv_blocks, n_blocks)), dim3(kTok), 0,
+                     stream, a, n_blocks);
   const int scale_blocks = std::min((T + kFinish - 1) / kFinish, kScaleBlocks);
   hipLaunchKernelGGL(grpo_scale_kernel, dim3(1 + scale_blocks), dim3(kFinish), 0, stream, a,
                      n_blocks);
