@@ -7,6 +7,7 @@
 #include <mutex>
 #include <sstream>
 
+#include "bwd_plan.h"
 #include "mv_internal.h"
 
 namespace mv {
@@ -61,8 +62,7 @@ hipError_t launch_attn_fwd(const mv_view_mask& m, int Hq, int Hkv, int D, float 
 hipError_t launch_attn_bwd(const mv_view_mask& m, int Hq, int Hkv, int D, float scale,
                            const void* q, const void* k, const void* v, const void* o,
                            const void* dout, const float* lse, void* dq, void* dk, void* dv,
-                           void* ws, hipStream_t stream, bool profile = true);
-size_t attn_bwd_ws_bytes(const mv_view_mask& m, int Hq, int Hkv, int D);
+                           void* ws, const BwdPlan& plan, hipStream_t stream, bool profile = true);
 hipError_t attn_bwd_scratch(void** ptr);
 hipError_t launch_materialize(const mv_view_mask& m, int row_begin, int row_end, uint32_t* bits,
                               hipStream_t stream);
@@ -240,7 +240,7 @@ mv_status mv_attn_fwd(const mv_view_mask* m, const mv_attn_shape* s, const void*
 
 size_t mv_attn_bwd_workspace_bytes(const mv_view_mask* m, const mv_attn_shape* s) {
   if (m == nullptr || s == nullptr || check_attn(m, s) != MV_OK) return 0;
-  return mv::attn_bwd_ws_bytes(*m, s->n_heads_q, s->n_heads_kv, s->head_dim);
+  return mv::bwd_plan(*m, s->n_heads_q, s->n_heads_kv, s->head_dim).ws_bytes;
 }
 
 mv_status mv_attn_bwd(const mv_view_mask* m, const mv_attn_shape* s, const void* q, const void* k,
@@ -248,7 +248,8 @@ mv_status mv_attn_bwd(const mv_view_mask* m, const mv_attn_shape* s, const void*
                       void* dk, void* dv, void* ws, size_t ws_bytes, hipStream_t stream) {
   if (mv_status st = check_attn(m, s); st != MV_OK) return st;
   if (mv_status st = check_ptrs({q, k, v, o, dout, lse, dq, dk, dv, ws}); st != MV_OK) return st;
-  const size_t need = mv::attn_bwd_ws_bytes(*m, s->n_heads_q, s->n_heads_kv, s->head_dim);
+  const mv::BwdPlan plan = mv::bwd_plan(*m, s->n_heads_q, s->n_heads_kv, s->head_dim);
+  const size_t need = plan.ws_bytes;
   if (ws_bytes < need) {
     std::ostringstream os;
     os << "attention backward workspace has " << ws_bytes << " bytes, needs " << need;
@@ -257,7 +258,7 @@ mv_status mv_attn_bwd(const mv_view_mask* m, const mv_attn_shape* s, const void*
   if (mv_status st = check_uploaded(m); st != MV_OK) return st;
   return hip_status(mv::launch_attn_bwd(*m, s->n_heads_q, s->n_heads_kv, s->head_dim,
                                         attn_scale(s), q, k, v, o, dout, lse, dq, dk, dv, ws,
-                                        stream),
+                                        plan, stream),
                     "attention backward launch");
 }
 
@@ -267,7 +268,8 @@ mv_status mv_attn_bwd_noalloc(const mv_view_mask* m, const mv_attn_shape* s, con
                               hipStream_t stream) {
   if (mv_status st = check_attn(m, s); st != MV_OK) return st;
   if (mv_status st = check_ptrs({q, k, v, o, dout, lse, dq, dk, dv}); st != MV_OK) return st;
-  const size_t need = mv::attn_bwd_ws_bytes(*m, s->n_heads_q, s->n_heads_kv, s->head_dim);
+  const mv::BwdPlan plan = mv::bwd_plan(*m, s->n_heads_q, s->n_heads_kv, s->head_dim);
+  const size_t need = plan.ws_bytes;
   if (need > MV_ATTN_BWD_NOALLOC_SCRATCH_BYTES) {
     std::ostringstream os;
     os << "attention backward needs " << need << " bytes of scratch; the static scratch of "
@@ -281,7 +283,7 @@ mv_status mv_attn_bwd_noalloc(const mv_view_mask* m, const mv_attn_shape* s, con
     return hip_status(e, "scratch address");
   return hip_status(mv::launch_attn_bwd(*m, s->n_heads_q, s->n_heads_kv, s->head_dim,
                                         attn_scale(s), q, k, v, o, dout, lse, dq, dk, dv, scratch,
-                                        stream, /*profile=*/false),
+                                        plan, stream, /*profile=*/false),
                     "attention backward launch");
 }
 

@@ -20,6 +20,7 @@
 #include <type_traits>
 #include <unordered_map>
 
+#include "bwd_plan.h"
 #include "mv_device.h"
 #include "mv_predicate.h"
 
@@ -27,22 +28,6 @@ namespace mv {
 
 namespace {
 constexpr float kLog2e = 1.4426950408889634f;
-// The dK/dV pass is cut into equal shares, one per CU, instead of running the
-// mask's work items, while those (times KV heads) are at most kShareMaxGroups:
-// few items of uneven length leave CUs idle.  dK/dV at 8192 tokens, 16 / 4
-// heads (388 items): 441 -> 335 us; 9500-token stream, 28 / 4 heads: 1121 ->
-// 1018 us; 16384 tokens, 28 / 4 heads (1208): whole layer 4820 -> 4446 us.
-// Shares lose the items' grouping by XCD (their L2 hit rate falls from 46% to
-// 15%), which costs more than the balance from there on: whole layer at 3992
-// items 7453 -> 7296 us, at 6048 items 11778 -> 11888 us.
-constexpr int kShareMaxGroups = 4096;
-constexpr int kShareMinSteps = 4;
-// With no more items than CUs the longest item bounds the pass; shares then
-// have to be this many steps shorter (the reduce launch and a run's start and
-// end take 8 steps' time: on 512 tokens, one head of 64, items of 8 steps and
-// 19 us became shares of 4 steps with 17 + 6 us, and stay items).
-constexpr int kShareExtra = 8;
-size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 }  // namespace
 
 struct BwdArgs {
@@ -57,21 +42,12 @@ struct BwdArgs {
   u16* dv;
   float* Dd;       // [Hq, T] -D = -rowsum(dO o O), written by the dQ pass
   float* L2;       // [Hq, T] LSE in base-2 units (LSE * log2 e), written by the dQ pass
-  float* partial;  // [n_slots, Hkv, 2, 128, D], or [2 workers, 2, 128, D]
+  float* partial;  // [n_slots, Hkv, 2, 128, D], or [the plan's partial tiles, 2, 128, D]
   mv_mask_dev mask;
   int T, Hq, Hkv, n_qt, n_items;
   float scale, scale_log2;
 };
 
-// The dK/dV pass cut into n equal shares: worker w takes the steps from cut w
-// to cut w + 1 of all steps laid end to end (KV head, key tile, query head,
-// query block).  Cut w: step st[w] of tile tile[w] = hk * n_kt + kt, with
-// st < the tile's steps (the last cut: tile n_kt * Hkv, step 0); cuts are
-// strictly increasing.
-struct SharePlan {
-  int n, n_kt;
-  int tile[kNumCu + 1], st[kNumCu + 1];
-};
 struct NoPlan {};
 
 // ---------------------------------------------------------------------------
@@ -637,17 +613,17 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(BwdArgs a, Plan plan) 
   xcd_split(xcd, local);
   if constexpr (SHARE) {
     // Every CU gets a share of the same cost whatever the tiles' lengths; at
-    // most its first and its last run are parts of a tile (partial tiles 2w
-    // and 2w + 1).  Neighbouring workers run on one XCD.
+    // most its first and its last run are parts of a tile.  Neighbouring
+    // workers run on one XCD.
     const int w = xcd * ((plan.n + kNumXcd - 1) / kNumXcd) + local;
     if (w >= plan.n) return;
-    int tile = plan.tile[w], st0 = plan.st[w];
-    const int tile1 = plan.tile[w + 1], st1 = plan.st[w + 1];
-    for (int first = 1; tile < tile1 || (tile == tile1 && st0 < st1); first = 0) {
+    int tile = plan.tile(w), st0 = plan.st[w], part = plan.part(w);
+    const int tile1 = plan.tile(w + 1), st1 = plan.st[w + 1];
+    while (tile < tile1 || (tile == tile1 && st0 < st1)) {
       const int hk = tile / plan.n_kt, kt = tile % plan.n_kt;
       const int nqb = a.mask.bwd_cum[kt + 1] - a.mask.bwd_cum[kt];
       const int n = (tile < tile1 ? nqb * G : st1) - st0;
-      segment(kt, hk, kt * (BK / BQ), nqb, st0, n, n == nqb * G ? -1 : 2 * w + 1 - first);
+      segment(kt, hk, kt * (BK / BQ), nqb, st0, n, n == nqb * G ? -1 : part++);
       ++tile;
       st0 = 0;
     }
@@ -666,8 +642,8 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(BwdArgs a, Plan plan) 
 // Sum the fp32 partial tiles of every split key tile in a fixed order.  A
 // block takes 1/kRedCut of a tile (dK and dV of one KV head): with a block
 // per tile, the 20 split tiles of an 8192-token trajectory filled a third of
-// the CUs.  Shares: the blocks of a tile's first cut sum the workers whose
-// shares meet it, in worker order.
+// the CUs.  Shares: the blocks of a tile's first cut sum the partial tiles of
+// the workers whose shares meet it, in worker order.
 constexpr int kRedCut = 8;
 template <int D, class Plan>
 __global__ __launch_bounds__(256) void bwd_reduce_kernel(BwdArgs a, Plan plan, int n_red) {
@@ -676,21 +652,18 @@ __global__ __launch_bounds__(256) void bwd_reduce_kernel(BwdArgs a, Plan plan, i
   constexpr size_t TILE = 2 * BK * D;     // floats of a partial tile
   const int cut = blockIdx.x % kRedCut, b = blockIdx.x / kRedCut;
   int kt, hk, n;
-  size_t p0, p1, stride;   // the first partial tile, the second, and the step from there on
+  size_t p0, stride;   // the first partial tile; floats from one to the next
   if constexpr (std::is_same<Plan, SharePlan>::value) {
     const int w = b + 1;   // the cut at the start of worker w's share
     if (w >= plan.n || plan.st[w] == 0) return;
-    const int tile = plan.tile[w];
-    const bool same = plan.tile[w - 1] == tile;   // worker w - 1 starts in this tile too
-    if (same && plan.st[w - 1] > 0) return;       // not the tile's first cut
-    for (n = 2; plan.tile[w + n - 1] == tile; ++n) {
+    const int tile = plan.tile(w);
+    if (plan.tile(w - 1) == tile && plan.st[w - 1] > 0) return;   // not the tile's first cut
+    for (n = 2; plan.tile(w + n - 1) == tile; ++n) {
     }
     kt = tile % plan.n_kt;
     hk = tile / plan.n_kt;
-    // the tile is the last run of worker w - 1, the first run of the others
-    p0 = 2 * (w - 1) + (same ? 0 : 1);
-    p1 = 2 * w;
-    stride = 2 * TILE;
+    p0 = plan.part(w) - 1;   // the last of worker w - 1
+    stride = TILE;
   } else {
     const int r = b / a.Hkv;
     hk = b % a.Hkv;
@@ -698,7 +671,6 @@ __global__ __launch_bounds__(256) void bwd_reduce_kernel(BwdArgs a, Plan plan, i
     kt = a.mask.bwd_red[r];
     p0 = size_t(a.mask.bwd_tiles[4 * kt + 2]) * a.Hkv + hk;
     n = a.mask.bwd_tiles[4 * kt + 3];
-    p1 = p0 + a.Hkv;
     stride = a.Hkv * TILE;
   }
   for (int e = cut * (N4 / kRedCut) + threadIdx.x; e < (cut + 1) * (N4 / kRedCut); e += 256) {
@@ -709,10 +681,10 @@ __global__ __launch_bounds__(256) void bwd_reduce_kernel(BwdArgs a, Plan plan, i
     if (key >= a.T) continue;
     // partials summed in order (the result does not depend on scheduling);
     // four loads in flight
-    float4 s = *reinterpret_cast<const float4*>(a.partial + p0 * TILE + size_t(e) * 4);
-    const float* p = a.partial + p1 * TILE + size_t(e) * 4;
-    int i = 0;
-    for (; i + 4 <= n - 1; i += 4) {
+    const float* p = a.partial + p0 * TILE + size_t(e) * 4;
+    float4 s = *reinterpret_cast<const float4*>(p);
+    int i = 1;
+    for (; i + 4 <= n; i += 4) {
       float4 x[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) x[u] = *reinterpret_cast<const float4*>(p + (i + u) * stride);
@@ -724,7 +696,7 @@ __global__ __launch_bounds__(256) void bwd_reduce_kernel(BwdArgs a, Plan plan, i
         s.w += x[u].w;
       }
     }
-    for (; i < n - 1; ++i) {
+    for (; i < n; ++i) {
       const float4 x = *reinterpret_cast<const float4*>(p + i * stride);
       s.x += x.x;
       s.y += x.y;
@@ -766,78 +738,10 @@ hipError_t attn_bwd_scratch(void** ptr) {
   return hipSuccess;
 }
 
-static size_t bwd_ws_bytes(const mv_view_mask& m, int Hq, int D, size_t n_partials) {
-  return 2 * align256(size_t(Hq) * m.T * sizeof(float)) +
-         align256(n_partials * 2 * kBwdTileK * D * sizeof(float)) + 256;
-}
-
-// Cost of a key tile's dK/dV steps in eighths of a fully visible step,
-// measured per worker on 8192-token trajectories (16 and 28 heads): a step
-// 2.1 - 2.5 us, a step that applies the mask 0.3 us more, and 10 us for each
-// run (its K and V, the first blocks' latency, its stores).
-constexpr int64_t kStepCost = 8, kRunCost = 32;
-
-// Workers of the dK/dV pass when it is cut into equal shares; 0: the mask's
-// work items, one workgroup each.
-static int bwd_workers(const mv_view_mask& m, int Hq, int Hkv, int D) {
-  const int64_t groups = int64_t(m.stats.bwd_items) * Hkv;
-  if (groups > kShareMaxGroups) return 0;
-  const int64_t steps = int64_t(m.bwd_cum.back()) * Hq;
-  int64_t n = std::min<int64_t>(kNumCu, (steps + kShareMinSteps - 1) / kShareMinSteps);
-  // never past the static scratch of the allocation-free form where the
-  // items' partial tiles fit it: that form takes the same calls either way
-  const size_t limit = MV_ATTN_BWD_NOALLOC_SCRATCH_BYTES;
-  if (bwd_ws_bytes(m, Hq, D, size_t(m.n_slots) * Hkv) <= limit)
-    while (n > 0 && bwd_ws_bytes(m, Hq, D, 2 * size_t(n)) > limit) --n;
-  if (n * 8 < std::min<int64_t>(kNumCu, groups) * 7) return 0;
-  if (groups <= kNumCu && steps / n + kShareExtra > int64_t(m.bwd_max_blocks) * (Hq / Hkv))
-    return 0;
-  return int(n);
-}
-
-static SharePlan share_plan(const mv_view_mask& m, int G, int Hkv, int workers) {
-  SharePlan p;
-  p.n_kt = m.n_kt128;
-  auto cost = [&](int kt) { return m.bwd_cost[kt] * G + kRunCost * kt; };   // of the tiles before kt
-  const int64_t per_kv = cost(p.n_kt);
-  int n = 0, kt = 0, hk = 0;
-  p.tile[0] = p.st[0] = 0;
-  for (int w = 1; w < workers; ++w) {
-    const int64_t pos = int64_t(w) * per_kv * Hkv / workers;
-    for (; (hk + 1) * per_kv <= pos; ++hk) kt = 0;
-    const int64_t r = pos - hk * per_kv;
-    while (cost(kt + 1) <= r) ++kt;
-    const int64_t steps = int64_t(m.bwd_cum[kt + 1] - m.bwd_cum[kt]) * G;
-    int tile = hk * p.n_kt + kt;
-    int st = int(((r - cost(kt)) * steps * 2 / (cost(kt + 1) - cost(kt)) + 1) / 2);   // nearest
-    if (st == steps) {
-      ++tile;
-      st = 0;
-    }
-    // a cut that falls on the one before it, or on the end, is dropped
-    if (tile == p.n_kt * Hkv || (tile == p.tile[n] && st == p.st[n])) continue;
-    ++n;
-    p.tile[n] = tile;
-    p.st[n] = st;
-  }
-  p.n = n + 1;
-  p.tile[p.n] = p.n_kt * Hkv;
-  p.st[p.n] = 0;
-  return p;
-}
-
-// D [Hq, T] | LSE * log2 e [Hq, T] | fp32 partials [n_slots, Hkv, 2, 128, D]
-// or [2 workers, 2, 128, D]; room for either, so that what the static scratch
-// refuses does not depend on the choice
-size_t attn_bwd_ws_bytes(const mv_view_mask& m, int Hq, int Hkv, int D) {
-  const size_t n = bwd_workers(m, Hq, Hkv, D);
-  return bwd_ws_bytes(m, Hq, D, std::max(2 * n, size_t(m.n_slots) * Hkv));
-}
-
 hipError_t launch_attn_bwd(const mv_view_mask& m, int Hq, int Hkv, int D, float scale,
                            const void* q, const void* k, const void* v, const void* o,
                            const void* dout, const float* lse, void* dq, void* dk, void* dv,
-                           void* ws, hipStream_t stream, bool profile) {
+                           void* ws, const BwdPlan& plan, hipStream_t stream, bool profile) {
   BwdArgs a;
   a.q = static_cast<const u16*>(q);
   a.k = static_cast<const u16*>(k);
@@ -869,26 +773,25 @@ hipError_t launch_attn_bwd(const mv_view_mask& m, int Hq, int Hkv, int D, float 
   // the general predicate only when some key has further live intervals
   const bool iv = !m.iv.empty();
   // dQ first: it writes the rows' -D and LSE * log2 e that dK/dV reads
-  auto run = [&](auto d_tag, auto iv_tag, const auto& plan, int groups, int n_red) {
+  auto run = [&](auto d_tag, auto iv_tag, const auto& div, int groups, int n_red) {
     constexpr int DD = decltype(d_tag)::value;
     constexpr bool IV = decltype(iv_tag)::value;
-    using Plan = std::decay_t<decltype(plan)>;
+    using Plan = std::decay_t<decltype(div)>;
     { ProfScope p("attn_bwd_dq", stream, profile);
       hipLaunchKernelGGL((bwd_dq_kernel<DD, IV>), g_dq, b256, 0, stream, a); }
     { ProfScope p("attn_bwd_dkdv", stream, profile);
       hipLaunchKernelGGL((bwd_dkdv_kernel<DD, IV, Plan>), dim3(groups), dim3(512), 0, stream, a,
-                         plan); }
+                         div); }
     if (n_red) {
       ProfScope p("attn_bwd_reduce", stream, profile);
       hipLaunchKernelGGL((bwd_reduce_kernel<DD, Plan>), dim3(unsigned(n_red) * kRedCut), b256, 0,
-                         stream, a, plan, n_red);
+                         stream, a, div, n_red);
     }
   };
   auto pick = [&](auto d_tag, auto iv_tag) {
-    const int workers = bwd_workers(m, Hq, Hkv, D);
-    if (workers) {
-      const SharePlan plan = share_plan(m, Hq / Hkv, Hkv, workers);
-      run(d_tag, iv_tag, plan, (plan.n + kNumXcd - 1) / kNumXcd * kNumXcd, plan.n - 1);
+    const SharePlan& share = plan.share;
+    if (share.n) {
+      run(d_tag, iv_tag, share, (share.n + kNumXcd - 1) / kNumXcd * kNumXcd, share.n - 1);
     } else {
       run(d_tag, iv_tag, NoPlan{}, (a.n_items + kNumXcd - 1) / kNumXcd * Hkv * kNumXcd,
           int(m.bwd_red.size()) * Hkv);

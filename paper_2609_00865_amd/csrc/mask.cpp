@@ -12,7 +12,7 @@
 #include <numeric>
 #include <sstream>
 
-#include "mv_internal.h"
+#include "bwd_plan.h"
 #include "mv_predicate.h"
 
 namespace {
@@ -316,7 +316,8 @@ void build_bwd_schedule(mv_view_mask& m) {
     // blocks the kernel takes without a mask: rows from the tile's last key
     // on, up to the first row some key is not live at
     const int32_t f0 = (j1 - 1 + BQ - 1) / BQ, f1 = std::min(qb1, lo / BQ);
-    m.bwd_cost.push_back(m.bwd_cost.back() + 8 * int64_t(n) + (n - std::max(0, f1 - f0)));
+    m.bwd_cost.push_back(m.bwd_cost.back() + mv::kStepCost * n +
+                         mv::kMaskCost * (n - std::max(0, f1 - f0)));
     m.bwd_tiles[4 * kt + 0] = lo;
     m.bwd_tiles[4 * kt + 1] = hi;
     if (chunks == 1) {
