@@ -4,6 +4,7 @@
 #pragma once
 
 #include <algorithm>
+#include <array>
 #include <cstddef>
 #include <cstdint>
 
@@ -38,14 +39,10 @@ struct SharePlan {
 // layer at 3992 items 7453 -> 7296 us, at 6048 items 11778 -> 11888 us).
 constexpr int kShareMaxGroups = 4096;
 constexpr int kShareMinSteps = 4;
-// With no more items than CUs the longest item bounds the pass; shares then
-// have to be this many steps shorter (the reduce launch and a run's start and
-// end take 8 steps' time: on 512 tokens, one head of 64, items of 8 steps and
-// 19 us became shares of 4 steps with 17 + 6 us, and stay items).
-constexpr int kShareExtra = 8;
 // Costs in eighths of a fully visible step (2.1 - 2.5 us at head size 128); a
 // step that applies the mask costs 0.3 us more, and a run 10 us (its K and V,
-// the first blocks' latency, its stores).
+// the first blocks' latency, its stores).  The reduce pass of the shares' P
+// partial tiles costs 16 + P / 10.
 constexpr int64_t kStepCost = 8, kMaskCost = 1, kRunCost = 32;
 
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -102,23 +99,80 @@ inline SharePlan share_plan(const mv_view_mask& m, int G, int Hkv, int workers) 
   return p;
 }
 
+// Cost of the longest share.
+inline double share_time(const mv_view_mask& m, const SharePlan& p, int G) {
+  const double per_kv = double(tiles_cost(m, G, p.n_kt));
+  double most = 0, from = 0;
+  for (int w = 1, hk = 0; w <= p.n; ++w) {
+    // cost of the steps before cut w and of the runs they make
+    while (p.tile(w) >= (hk + 1) * p.n_kt) ++hk;
+    const int kt = p.tile(w) - hk * p.n_kt;
+    double to = hk * per_kv + double(tiles_cost(m, G, kt));
+    if (p.st[w] > 0)
+      to += kRunCost + double((m.bwd_cost[kt + 1] - m.bwd_cost[kt]) * p.st[w]) /
+                           (m.bwd_cum[kt + 1] - m.bwd_cum[kt]);
+    most = std::max(most, to - from + (p.st[w - 1] > 0 ? kRunCost : 0));
+    from = to;
+  }
+  return most;
+}
+
+// Cost of the pass as work items: the dispatcher deals items to the XCDs
+// round-robin and each XCD gives the next to its first free CU.  Of the XCD
+// with the most work.
+inline int64_t items_time(const mv_view_mask& m, int G, int Hkv) {
+  const int n = int(m.bwd_item_cost.size());
+  auto cost = [&](int w) { return int64_t(m.bwd_item_cost[w]) * G + kRunCost; };
+  int64_t most = -1;
+  int xcd = 0;
+  for (int x = 0; x < std::min(n, kNumXcd); ++x) {
+    int64_t sum = 0;
+    for (int w = x; w < n; w += kNumXcd) sum += cost(w);
+    if (sum > most) {
+      most = sum;
+      xcd = x;
+    }
+  }
+  std::array<int64_t, kNumCu / kNumXcd> free_at{};   // a heap, the earliest first
+  constexpr int N = int(free_at.size());
+  int64_t end = 0;
+  for (int w = xcd; w < n; w += kNumXcd)
+    for (int hk = 0; hk < Hkv; ++hk) {
+      const int64_t t = free_at[0] + cost(w);
+      end = std::max(end, t);
+      int i = 0;
+      for (int c; (c = 2 * i + 1) < N; i = c) {
+        if (c + 1 < N && free_at[c + 1] < free_at[c]) ++c;
+        if (free_at[c] >= t) break;
+        free_at[i] = free_at[c];
+      }
+      free_at[i] = t;
+    }
+  return end;
+}
+
 struct BwdPlan {
   SharePlan share;   // n = 0: the mask's work items, one workgroup each
   size_t ws_bytes;   // of the backward's workspace
 };
 
-// Equal shares while the work items are few (kShareMaxGroups): few items of
-// uneven length leave CUs idle.  dK/dV at 8192 tokens, 16 / 4 heads (388
-// items): 441 -> 335 us; 9500-token stream, 28 / 4 heads: 1121 -> 1018 us;
-// 16384 tokens, 28 / 4 heads (1208): whole layer 4820 -> 4446 us.
+// Equal shares where the work items would leave CUs idle: where by the costs
+// above these take over 9/8 of the longest share's time (shares make less of
+// L2) and the reduce pass.  dK/dV and reduce at head size 128, items ->
+// shares, with the items' cost over the share's: 8192 tokens, 16 / 4 heads
+// (1.38): 428 -> 333 us; 2048 tokens, 32 / 8 heads (3.0): 202 -> 91; 4 x 3000
+// tokens, 32 / 8 heads (1.35): 687 -> 590; 16384 tokens, 28 / 4 heads (1.14):
+// 1869 -> 1767.  But 4 x 8192 tokens, 28 / 4 heads (1.08): 2450 -> 2467, 16 x
+// 2048 (1.08): 962 -> 1031, 32 x 1024 (1.01): 557 -> 594, 8 x 1024, 32 / 8
+// heads (0.99): 160 -> 180, and one trajectory of 878 tokens, 12 / 12 heads
+// (147 against 105, 192 partial tiles): 34 -> 38.
 inline BwdPlan bwd_plan(const mv_view_mask& m, int Hq, int Hkv, int D) {
   const int G = Hq / Hkv;
   const size_t items_ws = bwd_ws_bytes(m, Hq, D, size_t(m.n_slots) * Hkv);
   BwdPlan p;
   p.share.n = 0;
   p.ws_bytes = items_ws;
-  const int64_t groups = int64_t(m.stats.bwd_items) * Hkv;
-  if (groups > kShareMaxGroups) return p;
+  if (int64_t(m.stats.bwd_items) * Hkv > kShareMaxGroups) return p;
   const int64_t steps = int64_t(m.bwd_cum.back()) * Hq;
   int n = int(std::min<int64_t>(kNumCu, (steps + kShareMinSteps - 1) / kShareMinSteps));
   // The allocation-free form takes the same calls, with the same bits, either
@@ -135,8 +189,7 @@ inline BwdPlan bwd_plan(const mv_view_mask& m, int Hq, int Hkv, int D) {
     n -= std::max(1, int((ws - limit) / (size_t(4) * kBwdTileK * D * sizeof(float))));
   }
   if (s.n < 2) return p;
-  if (n * 8 < std::min<int64_t>(kNumCu, groups) * 7) return p;
-  if (groups <= kNumCu && steps / n + kShareExtra > int64_t(m.bwd_max_blocks) * G) return p;
+  if (items_time(m, G, Hkv) <= share_time(m, s, G) * 9 / 8 + 16 + s.part(s.n) * 0.1) return p;
   p.share = s;
   p.ws_bytes = std::max(items_ws, ws);
   return p;

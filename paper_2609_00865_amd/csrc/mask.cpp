@@ -292,6 +292,17 @@ void build_fwd_schedule(mv_view_mask& m) {
   m.stats.tiles_skipped = int32_t(skipped);
 }
 
+// Cost of the dK/dV steps of query blocks [qb0, qb1) and a key tile with keys
+// up to j1 - 1, all live up to row lo, per query head (the units of bwd_plan.h).
+int32_t dkdv_cost(int32_t j1, int32_t lo, int32_t qb0, int32_t qb1) {
+  const int32_t BQ = mv::kBwdBlockQ;
+  // blocks the kernel takes without a mask: rows from the tile's last key on,
+  // up to the first row some key is not live at
+  const int32_t f0 = std::max(qb0, (j1 - 1 + BQ - 1) / BQ), f1 = std::min(qb1, lo / BQ);
+  const int32_t n = qb1 - qb0, masked = n - std::max(0, f1 - f0);
+  return int32_t(mv::kStepCost) * n + int32_t(mv::kMaskCost) * masked;
+}
+
 void build_bwd_schedule(mv_view_mask& m) {
   const int32_t T = m.T, BK = mv::kBwdTileK, BQ = mv::kBwdBlockQ, CH = mv::kBwdChunk;
   m.n_kt128 = (T + BK - 1) / BK;
@@ -313,11 +324,7 @@ void build_bwd_schedule(mv_view_mask& m) {
     const int32_t qb0 = j0 / BQ, qb1 = (hi + BQ - 1) / BQ;
     const int32_t n = qb1 - qb0, chunks = (n + CH - 1) / CH;
     m.bwd_cum.push_back(m.bwd_cum.back() + n);
-    // blocks the kernel takes without a mask: rows from the tile's last key
-    // on, up to the first row some key is not live at
-    const int32_t f0 = (j1 - 1 + BQ - 1) / BQ, f1 = std::min(qb1, lo / BQ);
-    m.bwd_cost.push_back(m.bwd_cost.back() + mv::kStepCost * n +
-                         mv::kMaskCost * (n - std::max(0, f1 - f0)));
+    m.bwd_cost.push_back(m.bwd_cost.back() + dkdv_cost(j1, lo, qb0, qb1));
     m.bwd_tiles[4 * kt + 0] = lo;
     m.bwd_tiles[4 * kt + 1] = hi;
     if (chunks == 1) {
@@ -367,10 +374,11 @@ void build_bwd_schedule(mv_view_mask& m) {
     items[p] = order[q];
   }
   int64_t bwd_pairs = 0;
-  m.bwd_max_blocks = 0;
+  m.bwd_item_cost.clear();
   for (const auto& it : items) {
     bwd_pairs += int64_t(it[2] - it[1]) * BQ * BK;
-    m.bwd_max_blocks = std::max(m.bwd_max_blocks, it[2] - it[1]);
+    m.bwd_item_cost.push_back(dkdv_cost(std::min(T, (it[0] + 1) * BK), m.bwd_tiles[4 * it[0]],
+                                        it[1], it[2]));
   }
   m.stats.bwd_tile_pairs = bwd_pairs;
   m.bwd_items.reserve(items.size() * 4);

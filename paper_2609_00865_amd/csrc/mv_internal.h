@@ -64,10 +64,10 @@ struct mv_view_mask {
   int32_t n_qt = 0, n_kt64 = 0, n_kt128 = 0;
   std::vector<int32_t> omega, kt_minmax, q_ptr, k_list, qt_order;
   std::vector<int32_t> bwd_items, bwd_tiles, bwd_red, bwd_cum;
-  // cost of the dK/dV steps of the key tiles before, per query head: 8 a
-  // 64-row block, 1 more if the block needs the mask (host only)
+  // cost of dK/dV steps per query head, in the units of bwd_plan.h: of the key
+  // tiles before, and of each work item (host only)
   std::vector<int64_t> bwd_cost;
-  int32_t bwd_max_blocks = 0;       // 64-row blocks of the longest dK/dV work item
+  std::vector<int32_t> bwd_item_cost;
   std::vector<int32_t> iv_ptr, iv;  // further live intervals of restored keys
   int32_t n_slots = 0;
   int32_t kind = MV_VIEW_LIVE;
