@@ -45,19 +45,13 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "lm_plan.h"
 #include "mv_grpo_dev.h"
 
 namespace mv {
 
 namespace {
-constexpr int BA = 256, BT = 256, BKK = 64;
-// dH reads W itself up to this many tokens: the transposed copy costs its one
-// pass over W whatever the tokens (0.40 ms at 152064 x 3584), the product on
-// it runs 13% faster (4001 tokens: 3.09 against 3.53 ms; 1384 leaves: 1.12
-// against 1.30 ms; 32768 tokens: 22.7 against 25.9 ms).
-constexpr int kMaxDirectDh = 3072;
-constexpr int kMaxDhBlocks = 2048;         // output tiles times splits
-constexpr int kMaxDhSplits = 32;           // fp32 partials of a dH product split over the vocabulary
+constexpr int BA = kLmTileA, BT = kLmTileT, BKK = kLmSliceK;
 constexpr int NWAVES = 8;                  // waves per tile (2 x 4 grid)
 // token tiles per raster group: 8 x 4 A tiles run side by side on an XCD
 // for the products over the hidden dimension (measured ~1% faster than
@@ -79,8 +73,7 @@ __host__ __device__ inline size_t panel_index(int r, int k, int K) {
 }
 constexpr int FB = 4;                              // 16-row MFMA blocks per wave: tokens
 static_assert(4 * NWAVES * 1024 == SLICE_B, "two regions of two 1 KiB loads per wave");
-size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
-int vocab_pad(int V) { return (V + BA - 1) / BA * BA; }
+size_t align256(size_t x) { return lm_align256(x); }
 }  // namespace
 
 enum { kModeLogits = 0, kModeGrad = 1, kModeDh = 2, kModeKL = 3, kModeKLGrad = 4, kModeDhW = 5 };
@@ -112,7 +105,6 @@ struct LmArgs {
   const float* dkl;   // [n] upstream gradient of each leaf's KL
   int n_leaves, n_rows_T, n_rows_S;
   int T, H, V, Vp, n_chunks;
-  int Tg;              // rows of G: T rounded up to a multiple of 256 (zero past T)
   int nA, nT;         // tiles along the A side and along tokens
   // dH mode split over the vocabulary (K) when there are too few output
   // tiles to fill the chip: split s covers k slices [s*nk_split, ...) and
@@ -431,7 +423,7 @@ __global__ __launch_bounds__(NWAVES * 64, 1) void lm_tile_kernel(LmArgs a) {
     }
   } else if (MODE == kModeGrad) {
     // -g_t softmax(z_t)_v everywhere (zero in the vocabulary padding; rows
-    // T .. Tg - 1, which pad the dW product's k, are zeros too); the target
+    // past T, which pad the dW product's k, are zeros too); the target
     // entry gets its one-hot term from lm_target_kernel afterwards.  The
     // tile's block of G is one contiguous 128 KiB run of four panels: it is
     // assembled in LDS in that order (the 16-byte chunks of each 128-byte
@@ -916,68 +908,6 @@ __global__ __launch_bounds__(256) void kl_combine_kernel(LmArgs a, float* kl, fl
   kl[leaf] = cr / st + ((ms - mt) + (l2s - l2t)) * kLn2;
 }
 
-// Vocabulary splits for a dH product: none when the output tiles already
-// cover the CUs several times, otherwise the count with the least time, of
-// rounds of 256 resident blocks at 1.4 us a slice (a block's slice measured
-// 1.35 - 1.45 us) and the fp32 partials' way out and back at 4 TB/s.  (With at
-// most 8 splits, whatever they left idle, 777 tokens x 1024 x 32000 ran 128
-// blocks: dH 87 us.)
-static int dh_splits(int n_tokens, int H, int V) {
-  const int tiles = ((H + BA - 1) / BA) * ((n_tokens + BT - 1) / BT);
-  if (tiles >= 4 * kNumCu || tiles == 0) return 1;
-  const int nk = (V + BKK - 1) / BKK;
-  const double part_us = double(n_tokens) * H * 8 / 4e6;   // one split's partial, both ways
-  int best = 1;
-  double best_t = 0;
-  for (int s = 1; s <= kMaxDhSplits && s <= nk && tiles * s <= kMaxDhBlocks; ++s) {
-    const double t = double((int64_t(tiles) * s + kNumCu - 1) / kNumCu) * ((nk + s - 1) / s) * 1.4 +
-                     (s > 1 ? s * part_us : 0.0);
-    if (s == 1 || t < 0.97 * best_t) {
-      best_t = t;
-      best = s;
-    }
-  }
-  return best;
-}
-
-// Room for the partials: an upper bound of splits * T * H floats that never
-// shrinks as T grows (splits <= kMaxDhSplits, tiles * splits <= kMaxDhBlocks),
-// so that a workspace sized for some tokens serves any fewer.
-static size_t dh_part_bytes(int T, int H) {
-  return align256(std::min(size_t(kMaxDhSplits) * T * H, size_t(kMaxDhBlocks) * BA * BT) *
-                  sizeof(float));
-}
-
-// Whether the products over the hidden dimension take 128-row vocabulary
-// tiles instead of 256: only when twice as many tiles still run at once.  A
-// tile of half the rows takes 0.73 of the time (it has half the bytes of W in
-// flight): 100 tokens x 1024 x 32000 (125 tiles), training step: 141 -> 130
-// us, 100 leaves: 94 -> 84 us; but 201 tokens x 3584 x 152064 (594 tiles, 3
-// rounds of resident blocks against 5 half ones), scoring: 273 -> 320 us.
-static bool half_tiles(int n_tokens, int V) {
-  return 2 * int64_t(vocab_pad(V) / BA) * ((n_tokens + BT - 1) / BT) <= kNumCu;
-}
-// vocabulary tiles (each holds some row < V: a tile clamps its rows to V - 1)
-static int tiles_a(int n_tokens, int V) {
-  const int rows = half_tiles(n_tokens, V) ? 128 : BA;
-  return (V + rows - 1) / rows;
-}
-// partials of the logits pass at most where its tiles are 128 rows (KL: half)
-constexpr size_t kHalfPartials = size_t(BT) * 2 * kNumCu;
-// per-token partials of the logits and KL passes: one per tile and wave row
-static int n_chunks_of(int n_tokens, int V) { return 2 * tiles_a(n_tokens, V); }
-
-// rows of a panel-layout matrix
-static int panel_rows(int R) { return (R + 255) / 256 * 256; }
-
-// Whether the dH product reads W as it is, with transposing LDS reads, instead
-// of a transposed copy that the call first makes of it.
-static bool dh_direct(int n_tokens) { return n_tokens <= kMaxDirectDh; }
-
-static size_t wT_bytes(int n_tokens, int H, int V) {
-  return dh_direct(n_tokens) ? 0 : align256(size_t(panel_rows(H)) * vocab_pad(V) * sizeof(u16));
-}
-
 size_t kl_fwd_ws_bytes(int n, int H, int V) {
   const size_t np = std::max(size_t(n) * n_chunks_of(2 * n, V), kHalfPartials / 2);
   return align256(np * sizeof(float4)) + align256(np * sizeof(float2)) +
@@ -986,8 +916,7 @@ size_t kl_fwd_ws_bytes(int n, int H, int V) {
 
 // G [n, Vp] | dH partials | zero row [H] | W^T [H, Vp] unless direct (G and W^T in panels)
 size_t kl_bwd_ws_bytes(int n, int H, int V) {
-  return align256(size_t(panel_rows(n)) * vocab_pad(V) * sizeof(u16)) + dh_part_bytes(n, H) +
-         align256(size_t(H) * sizeof(u16)) + wT_bytes(n, H, V) + 256;
+  return g_and_part_bytes(n, H, V) + align256(size_t(H) * sizeof(u16)) + wT_bytes(n, H, V) + 256;
 }
 
 __global__ __launch_bounds__(256) void zero_u16_kernel(u16* p, int n) {
@@ -1026,12 +955,9 @@ size_t logprob_grpo_ws_bytes(int T, int H, int V, int n_traj) {
          align256(size_t(n_traj) * sizeof(float));
 }
 
-static int g_rows(int T) { return panel_rows(T); }
-
-// status | G [Tg, Vp] | dH partials | W^T [H, Vp] unless direct (G and W^T in panels)
+// status | G [T up to a multiple of 256, Vp] | dH partials | W^T [H, Vp] unless direct (G and W^T in panels)
 size_t logprob_bwd_ws_bytes(int T, int H, int V) {
-  return kStatusBytes + align256(size_t(g_rows(T)) * vocab_pad(V) * sizeof(u16)) +
-         dh_part_bytes(T, H) + wT_bytes(T, H, V) + 256;
+  return kStatusBytes + g_and_part_bytes(T, H, V) + wT_bytes(T, H, V) + 256;
 }
 
 static char* align_ptr(void* p) {
@@ -1099,7 +1025,7 @@ __global__ __launch_bounds__(256) void dh_reduce_kernel(const float* part, u16* 
 
 // dh[T, H] = G[T, Vp] W[Vp, H] (bf16 out) with b.wT = W^T [H, Vp], split over
 // the vocabulary when the output alone would leave CUs idle; `part` is the
-// fp32 partial area of the workspace (dh_part_bytes).
+// fp32 partial area of the workspace (g_and_part_bytes).
 static hipError_t launch_dh(LmArgs b, float* part, const char* name, hipStream_t stream) {
   const int nk_total = (b.V + BKK - 1) / BKK;   // G is zero past V
   int splits = dh_splits(b.T, b.H, b.V);
@@ -1273,12 +1199,11 @@ hipError_t launch_logprob_bwd(int T, int H, int V, const void* hidden, const voi
   a.H = H;
   a.V = V;
   a.Vp = vocab_pad(V);
-  a.Tg = g_rows(T);
   a.bad_targets = logprob_status_word(ws);   // cleared by the G pass
   char* base = align_ptr(ws) + kStatusBytes;
   u16* G = reinterpret_cast<u16*>(base);
-  float* part = reinterpret_cast<float*>(base + align256(size_t(a.Tg) * a.Vp * sizeof(u16)));
-  u16* wT = reinterpret_cast<u16*>(reinterpret_cast<char*>(part) + dh_part_bytes(T, H));
+  float* part = reinterpret_cast<float*>(base + g_bytes(T, V));
+  u16* wT = reinterpret_cast<u16*>(base + g_and_part_bytes(T, H, V));
   a.Gout = G;
   a.G = G;
   a.wT = wT;
@@ -1377,8 +1302,8 @@ hipError_t launch_kl_bwd(int n, int H, int V, const void* hT, int nT, const int3
   a.Vp = vocab_pad(V);
   char* base = align_ptr(ws);
   u16* G = reinterpret_cast<u16*>(base);
-  float* part = reinterpret_cast<float*>(base + align256(size_t(panel_rows(n)) * a.Vp * sizeof(u16)));
-  u16* zrow = reinterpret_cast<u16*>(reinterpret_cast<char*>(part) + dh_part_bytes(n, H));
+  float* part = reinterpret_cast<float*>(base + g_bytes(n, V));
+  u16* zrow = reinterpret_cast<u16*>(base + g_and_part_bytes(n, H, V));
   u16* wT = reinterpret_cast<u16*>(reinterpret_cast<char*>(zrow) + align256(size_t(H) * sizeof(u16)));
   a.Gout = G;
   a.nA = tiles_a(a.T, a.V);

@@ -51,3 +51,43 @@ def test_short_rollouts_keep_the_work_items():
         assert ws == 2 * hq * T * 4 + 256, (n, length, hq, hkv)
     # one such rollout leaves CUs idle
     assert _attn_ws([synth.Trajectory(0, 2048, ())], 32, 8, 128)[1] > 2 * 32 * 2048 * 4 + 256
+
+
+def test_lm_head_partials_fit_their_room(tmp_path):
+    """For every token count the dH partials fit what the workspace has for
+    them, and that never shrinks as tokens grow."""
+    _run(tmp_path, "lm_plan_check")
+
+
+LM_SHAPES = [(1024, 32000), (3584, 152064), (4096, 128256), (64, 1000)]
+
+
+def _lm_sizes(n, H, V, n_traj=8):
+    s = mv.LogprobShape(n, H, V, 0.2, 0.2)
+    g = mv.GrpoShape(n, n_traj, 8, 0.2, 0.2, 0.0, 1e-6)
+    k = mv.KLShape(n, H, V, 16384, 16384)
+    ref = ctypes.byref
+    return (mv.mv_token_logprob_workspace_bytes(ref(s)),
+            mv.mv_token_logprob_grpo_workspace_bytes(ref(s), ref(g)),
+            mv.mv_token_logprob_bwd_workspace_bytes(ref(s)),
+            mv.mv_sdcc_kl_workspace_bytes(ref(k)), mv.mv_sdcc_kl_bwd_workspace_bytes(ref(k)))
+
+
+def test_lm_head_workspaces_never_shrink():
+    for H, V in LM_SHAPES:
+        before = (0,) * 5
+        for n in sorted({*range(1, 3400, 3), *range(3071, 3075), *range(256, 33000, 256),
+                         *range(257, 33000, 256)}):
+            now = _lm_sizes(n, H, V)
+            assert all(a >= b for a, b in zip(now, before)), (n, H, V, now, before)
+            before = now
+
+
+def test_lm_head_backward_reserves_what_it_uses():
+    """Where dH is not split there is no room for partials: G and W^T alone
+    (with room for 32 splits whatever the count, 512 MiB more)."""
+    vp = 152064 // 256 * 256
+    both = 2 * vp * (32768 + 3584)
+    assert _lm_sizes(32768, 3584, 152064)[2] <= both + 4096
+    # three fp32 partials of the 1384 leaves' dh, beside G
+    assert _lm_sizes(1384, 3584, 152064)[4] <= 2 * vp * 1536 + 3 * 4 * 1384 * 3584 + 65536
