@@ -807,29 +807,33 @@ __global__ __launch_bounds__(256) void lm_combine_kernel(LmArgs a, CombineOut o)
     else if (lane == 0 && y != -1)
       atomicAdd(a.bad_targets, 1);
     const float2* p = a.part + size_t(t) * a.n_chunks;
-    // the lane's partials, read once, kMerge loads in flight
-    constexpr int kMerge = 8;
-    float m = -INFINITY, s = 0.f;
-    for (int i0 = lane; i0 < a.n_chunks; i0 += 64 * kMerge) {
-      float2 x[kMerge];
-      float mx = m;
+    // The lane's first partials are read once and held until the wave's
+    // maximum is known, so that no sum is rescaled (a running maximum, with a
+    // rescaled sum every eight partials, cost two roundings in the last place
+    // more); vocabularies past 64 kHeld chunks (196608) read the rest twice.
+    constexpr int kHeld = 24, kMerge = 8;
+    float2 x[kHeld];
+    float m = -INFINITY;
 #pragma unroll
-      for (int u = 0; u < kMerge; ++u) {
-        const int i = i0 + 64 * u;
-        x[u] = i < a.n_chunks ? p[i] : make_float2(-INFINITY, 0.f);
+    for (int u0 = 0; u0 < kHeld; u0 += kMerge) {
+#pragma unroll
+      for (int u = u0; u < u0 + kMerge; ++u) x[u] = make_float2(-INFINITY, 0.f);
+      if (64 * u0 < a.n_chunks) {   // wave-uniform
+#pragma unroll
+        for (int u = u0; u < u0 + kMerge; ++u)
+          if (lane + 64 * u < a.n_chunks) x[u] = p[lane + 64 * u];
       }
-#pragma unroll
-      for (int u = 0; u < kMerge; ++u) mx = fmaxf(mx, x[u].x);
-      const float mu = mx == -INFINITY ? 0.f : mx;   // chunks of padding only
-      s *= fast_exp2(m - mu);
-#pragma unroll
-      for (int u = 0; u < kMerge; ++u) s += x[u].y * fast_exp2(x[u].x - mu);
-      m = mx;
     }
-    const float m_lane = m;
+#pragma unroll
+    for (int u = 0; u < kHeld; ++u) m = fmaxf(m, x[u].x);
+    for (int i = lane + 64 * kHeld; i < a.n_chunks; i += 64) m = fmaxf(m, p[i].x);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-    s *= fast_exp2(m_lane - m);   // a lane without partials: 0 (and a NaN stays one)
+    float s = 0.f;
+#pragma unroll
+    for (int u = 0; u < kHeld; ++u)
+      if (64 * u < a.n_chunks) s += x[u].y * fast_exp2(x[u].x - m);   // no partial: + 0
+    for (int i = lane + 64 * kHeld; i < a.n_chunks; i += 64) s += p[i].y * fast_exp2(p[i].x - m);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
     if (lane == 0) {

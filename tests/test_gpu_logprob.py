@@ -64,6 +64,13 @@ def test_dh_product_forms(T, H, V):
     _check(*_inputs(T, H, V, 9, skip_every=11), f"dh{T}x{H}x{V}")
 
 
+@pytest.mark.parametrize("T,H,V", [(33, 64, 70001), (9, 64, 196608), (9, 64, 200100)])
+def test_vocabularies_of_many_chunks(T, H, V):
+    """The combine pass holds 24 partials a lane: three batches of eight (the
+    second partly empty, all full) and some past them."""
+    _check(*_inputs(T, H, V, 10, skip_every=4), f"lp{T}x{H}x{V}")
+
+
 def test_out_of_range_targets_are_skipped_and_counted():
     """Ids outside [-1, vocab) are never used as an index: their tokens are
     scored as tokens without loss (logp 0, ratio 1, zero dH) and counted in
