@@ -2,6 +2,8 @@
 oracle: full comparisons at sizes the oracle finishes quickly (several tiles
 and ragged tails), sampled rows and keys at the long workloads' full sizes,
 bit-exact mask bits, determinism, and negative controls."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -157,10 +159,51 @@ def test_backward_in_equal_shares(d, hq, hkv, lens, restore, seed):
     trajs = synth.random_trajectories(rng, lens, max_edits=6, max_span=200, summary_max=30,
                                       restore_max=restore)
     T = trajs[-1].end
+    need, items = _bwd_workspace(trajs, hq, hkv, d)
+    assert need > items        # shares were taken: they have partial tiles of their own
     gen = torch.Generator().manual_seed(seed)
     q, do = (torch.randn(T, hq, d, generator=gen).to(torch.bfloat16) for _ in range(2))
     k, v = (torch.randn(T, hkv, d, generator=gen).to(torch.bfloat16) for _ in range(2))
     _check_full(trajs, q, k, v, do, f"shares{lens}/d{d}/{hq}:{hkv}")
+
+
+def _bwd_workspace(trajs, hq, hkv, d):
+    """Workspace bytes of the backward, and what it takes when dK/dV runs the
+    mask's work items (row statistics and one partial tile per split item)."""
+    m = mv.ViewMask(trajs)
+    need = int(mv.mv_attn_bwd_workspace_bytes(
+        m.handle, ctypes.byref(mv.AttnShape(m.total_tokens, hq, hkv, d, 0.0))))
+    up = lambda x: -(-x // 256) * 256
+    return need, (2 * up(4 * hq * m.total_tokens) +
+                  up(m.stats()["bwd_partial_slots"] * hkv * 2 * 128 * d * 4) + 256)
+
+
+@pytest.mark.parametrize("d,G,restore,seed", [(64, 1, 0, 71), (64, 2, 60, 72), (128, 1, 60, 73)])
+def test_split_work_items(d, G, restore, seed):
+    """More work items than the shares take (28 KV heads, six trajectories of
+    2600 tokens): key tiles seen by more than 32 query blocks are cut into
+    items whose partial tiles the reduce pass sums.  The first, a middle and
+    the last KV head against the oracle."""
+    hkv, lens = 28, [2600] * 6
+    rng = np.random.default_rng(seed)
+    trajs = synth.random_trajectories(rng, lens, max_edits=6, max_span=200, summary_max=30,
+                                      restore_max=restore)
+    assert any(e.restore for t in trajs for e in t.edits) == bool(restore)
+    st = mv.ViewMask(trajs).stats()
+    assert st["bwd_items"] * hkv > 4096 and st["bwd_partial_slots"] > 0
+    T = trajs[-1].end
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    rand = lambda h: torch.randn(T, h, d, generator=gen, device="cuda").to(torch.bfloat16)
+    q, do, k, v = rand(hkv * G), rand(hkv * G), rand(hkv), rand(hkv)
+    _, g = _run(trajs, q, k, v, do)
+    kv = torch.tensor([0, 13, hkv - 1])
+    heads = (kv[:, None] * G + torch.arange(G)).reshape(-1)
+    c = lambda x, h: x.cpu()[:, h].to(F64)
+    O, _, dQ, dK, dV = OA.logittree(trajs, c(q, heads), c(k, kv), c(v, kv), dout=c(do, heads),
+                                    row_chunk=1024)
+    what = f"split items/d{d}/G{G}"
+    for name, h, ref in (("o", heads, O), ("dq", heads, dQ), ("dk", kv, dK), ("dv", kv, dV)):
+        assert_bf16_close(g[name].cpu()[:, h], ref, f"{what} {name}")
 
 
 @pytest.mark.parametrize("d", [128, 64])

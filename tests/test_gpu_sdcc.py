@@ -82,6 +82,20 @@ def test_small_ragged(n_rows, H, V):
     _check(hT, rT, hS, rS, w, dkl[:rT.numel()], f"kl{n_rows}x{H}x{V}")
 
 
+@pytest.mark.parametrize("n,H,V", [
+    (3072, 64, 1400), (3073, 64, 1400),   # the last count whose dh reads W itself, the first on
+                                          # W^T; 256-row vocabulary tiles
+    (3073, 64, 300),                      # W^T after a G of 128-row tiles
+    (40, 64, 32769), (200, 128, 17000),   # 256-row tiles (the last of one row), one and two
+                                          # tiles of leaf rows
+])
+def test_product_forms(n, H, V):
+    gen = torch.Generator().manual_seed(n + V)
+    hT, hS, w, dkl = _hidden(n, H, V, 13)
+    rT, rS = (torch.randint(0, n, (n,), generator=gen).to(torch.int32) for _ in range(2))
+    _check(hT, rT, hS, rS, w, dkl, f"kl{n}x{H}x{V}")
+
+
 def test_single_leaf():
     hT, hS, w, dkl = _hidden(4, 64, 300, 3)
     rT = torch.tensor([2], dtype=torch.int32)
