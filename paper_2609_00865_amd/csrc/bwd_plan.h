@@ -40,10 +40,11 @@ struct SharePlan {
 constexpr int kShareMaxGroups = 4096;
 constexpr int kShareMinSteps = 4;
 // Costs in eighths of a fully visible step (2.1 - 2.5 us at head size 128); a
-// step that applies the mask costs 0.3 us more, and a run 10 us (its K and V,
-// the first blocks' latency, its stores).  The reduce pass of the shares' P
-// partial tiles costs 16 + P / 10.
-constexpr int64_t kStepCost = 8, kMaskCost = 1, kRunCost = 32;
+// step that applies the mask costs 0.3 us more, a run 10 us (its K and V, the
+// first blocks' latency, its stores), a work item that leaves a partial tile
+// as much again, and a reduce pass of P partial tiles 16 + P / 10.
+constexpr int64_t kStepCost = 8, kMaskCost = 1, kRunCost = 32, kPartCost = 32;
+inline double reduce_cost(int64_t parts) { return parts > 0 ? 16 + parts * 0.1 : 0.0; }
 
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
@@ -120,9 +121,11 @@ inline double share_time(const mv_view_mask& m, const SharePlan& p, int G) {
 // Cost of the pass as work items: the dispatcher deals items to the XCDs
 // round-robin and each XCD gives the next to its first free CU.  Of the XCD
 // with the most work.
-inline int64_t items_time(const mv_view_mask& m, int G, int Hkv) {
+inline double items_time(const mv_view_mask& m, int G, int Hkv) {
   const int n = int(m.bwd_item_cost.size());
-  auto cost = [&](int w) { return int64_t(m.bwd_item_cost[w]) * G + kRunCost; };
+  auto cost = [&](int w) {
+    return int64_t(m.bwd_item_cost[w]) * G + kRunCost + (m.bwd_items[4 * w + 3] < 0 ? 0 : kPartCost);
+  };
   int64_t most = -1;
   int xcd = 0;
   for (int x = 0; x < std::min(n, kNumXcd); ++x) {
@@ -148,7 +151,7 @@ inline int64_t items_time(const mv_view_mask& m, int G, int Hkv) {
       }
       free_at[i] = t;
     }
-  return end;
+  return double(end);
 }
 
 struct BwdPlan {
@@ -156,16 +159,24 @@ struct BwdPlan {
   size_t ws_bytes;   // of the backward's workspace
 };
 
-// Equal shares where the work items would leave CUs idle: where by the costs
-// above these take over 9/8 of the longest share's time (shares make less of
-// L2) and the reduce pass.  dK/dV and reduce at head size 128, items ->
-// shares, with the items' cost over the share's: 8192 tokens, 16 / 4 heads
-// (1.38): 428 -> 333 us; 2048 tokens, 32 / 8 heads (3.0): 202 -> 91; 4 x 3000
-// tokens, 32 / 8 heads (1.35): 687 -> 590; 16384 tokens, 28 / 4 heads (1.14):
-// 1869 -> 1767.  But 4 x 8192 tokens, 28 / 4 heads (1.08): 2450 -> 2467, 16 x
-// 2048 (1.08): 962 -> 1031, 32 x 1024 (1.01): 557 -> 594, 8 x 1024, 32 / 8
-// heads (0.99): 160 -> 180, and one trajectory of 878 tokens, 12 / 12 heads
-// (147 against 105, 192 partial tiles): 34 -> 38.
+// Whether equal shares beat the work items by the costs above.  Shares make
+// less of L2 and cannot even out what the costs miss: they have to be 10%
+// shorter, with interval lists 25% (a step's cost then varies with its lists).
+// dK/dV and reduce, items -> shares, with the items' cost over the share's:
+// 8192 tokens, 16 / 4 heads (1.38): 428 -> 333 us; 2048 tokens, 32 / 8 heads
+// (3.0): 202 -> 91; 4 x 3000 tokens, 32 / 8 heads (1.35): 687 -> 590; 18230
+// tokens, 28 / 4 heads (1.13): 2144 -> 1963.  But 16 x 2048 tokens, 28 / 4
+// heads (1.08): 962 -> 1031, 32 x 1024 (1.01): 557 -> 594, 8 x 1024, 32 / 8
+// heads (0.99): 160 -> 180, 878 tokens, 12 / 12 heads (147 against 105 and 192
+// partial tiles): 34 -> 38, and 23286 tokens in three trajectories with
+// restores, 8 / 2 heads of 64 (1.12): 1760 -> 2088.  Over 126 shapes the better
+// form is missed by 0.2% on average and 5% at most.
+inline bool shares_pay(const mv_view_mask& m, const SharePlan& p, int G, int Hkv) {
+  const double lead = m.iv.empty() ? 1.1 : 1.25;
+  return items_time(m, G, Hkv) + reduce_cost(int64_t(m.n_slots) * Hkv) >
+         share_time(m, p, G) * lead + reduce_cost(p.part(p.n));
+}
+
 inline BwdPlan bwd_plan(const mv_view_mask& m, int Hq, int Hkv, int D) {
   const int G = Hq / Hkv;
   const size_t items_ws = bwd_ws_bytes(m, Hq, D, size_t(m.n_slots) * Hkv);
@@ -189,7 +200,7 @@ inline BwdPlan bwd_plan(const mv_view_mask& m, int Hq, int Hkv, int D) {
     n -= std::max(1, int((ws - limit) / (size_t(4) * kBwdTileK * D * sizeof(float))));
   }
   if (s.n < 2) return p;
-  if (items_time(m, G, Hkv) <= share_time(m, s, G) * 9 / 8 + 16 + s.part(s.n) * 0.1) return p;
+  if (!shares_pay(m, s, G, Hkv)) return p;
   p.share = s;
   p.ws_bytes = std::max(items_ws, ws);
   return p;
