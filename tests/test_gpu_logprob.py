@@ -64,10 +64,12 @@ def test_dh_product_forms(T, H, V):
     _check(*_inputs(T, H, V, 9, skip_every=11), f"dh{T}x{H}x{V}")
 
 
-@pytest.mark.parametrize("T,H,V", [(33, 64, 70001), (9, 64, 196608), (9, 64, 200100)])
+@pytest.mark.parametrize("T,H,V", [(33, 64, 65536), (33, 64, 70001), (9, 64, 196608),
+                                   (9, 64, 200100), (9, 64, 262144), (9, 64, 263000)])
 def test_vocabularies_of_many_chunks(T, H, V):
-    """The combine pass holds 24 partials a lane: three batches of eight (the
-    second partly empty, all full) and some past them."""
+    """The combine pass holds 8, 24 or 32 partials a lane, in batches of eight:
+    the last and the first vocabulary of each form (batches full, partly and
+    wholly empty), and one with partials past the 32."""
     _check(*_inputs(T, H, V, 10, skip_every=4), f"lp{T}x{H}x{V}")
 
 
