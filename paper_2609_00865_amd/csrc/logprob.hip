@@ -31,11 +31,11 @@
 // matrix pipe is not waiting behind LDS reads, and quarter by quarter the
 // slice's LDS regions are free for the slice after next (a load has 1.5
 // slices to land).  Bound by the matrix pipe at the clock the chip holds
-// under it: at 32768 tokens x 3584 x 152064 the pipe is busy 83% (logits),
-// 75% (G) and 93% (dH) of the cycles at 1.63-1.8 GHz, where the earlier loop
+// under it: at 32768 tokens x 3584 x 152064 the pipe is busy 82% (logits),
+// 74% (G) and 93% (dH) of the cycles at 1.6-1.8 GHz, where the earlier loop
 // (both waves reading, then both in MFMAs; one barrier per slice) had
-// 56-64%.  At 4001 tokens: logits 3.60 -> 3.18 ms, G 3.74 -> 3.23, dH 3.54 ->
-// 3.09; at 32768: 26.1 -> 23.5, 27.8 -> 24.9, 25.7 -> 22.7 ms.  An
+// 56-64%.  Both timed in turn: at 4001 tokens logits 3.54 -> 3.22 ms, G 3.73 ->
+// 3.20, dH 3.50 -> 3.11; at 32768: 26.7 -> 24.5, 28.6 -> 26.0, 26.0 -> 23.1.  An
 // operand slice sits in LDS as [256 rows][64] bf16 without padding, with
 // 16-byte chunk c of row r at chunk position c ^ (r & 7): the fragment reads
 // (16 lanes = 16 consecutive rows at one chunk) hit distinct banks.  Tiles are
@@ -422,13 +422,13 @@ __global__ __launch_bounds__(NWAVES * 64, 1) void lm_tile_kernel(LmArgs a) {
       if (lane < 16 && t < a.T) a.part[size_t(t) * a.n_chunks + chunk] = make_float2(m2, s);
     }
   } else if (MODE == kModeGrad) {
-    // -g_t softmax(z_t)_v everywhere (zero in the vocabulary padding; rows
+    // -g_t softmax(z_t)_v everywhere (zero from V to the tile's end; rows
     // past T, which pad the dW product's k, are zeros too); the target
     // entry gets its one-hot term from lm_target_kernel afterwards.  The
-    // tile's block of G is one contiguous 128 KiB run of four panels: it is
-    // assembled in LDS in that order (the 16-byte chunks of each 128-byte
-    // row permuted by the row's low bits, against bank conflicts) and written
-    // with 16-byte stores that cover whole lines.
+    // tile's block of G is one contiguous run of TA / 64 panels (128 or 64
+    // KiB): it is assembled in LDS in that order (the 16-byte chunks of each
+    // 128-byte row permuted by the row's low bits, against bank conflicts) and
+    // written with 16-byte stores that cover whole lines.
     char* sg = reinterpret_cast<char*>(smem);
     __syncthreads();   // every wave has read its last operand fragments
 #pragma unroll
@@ -580,7 +580,8 @@ __global__ __launch_bounds__(NWAVES * 64, 1) void lm_tile_kernel(LmArgs a) {
 // 256 (the grad pass writes them), so the last slice needs no masking: H rows
 // past T are read clamped and meet zero G rows.  Bound as the tile engine: at
 // 32768 tokens x 3584 x 152064 the loop in which both waves of a SIMD read and
-// multiplied together took 30.9 ms with the pipe 64% busy, this one 26.6 ms.
+// multiplied together took 31.7 ms with the pipe 64% busy, this one 28.3 ms
+// with 85%.
 __global__ __launch_bounds__(NWAVES * 64, 1) void lm_dw_kernel(LmArgs a) {
   __shared__ __align__(1024) u16 smem[2 * 2 * SLICE_B / 2];   // (G, H) x 2 slices
   constexpr int SUB = 64 * 128;   // bytes of a sub-tile
@@ -1037,7 +1038,9 @@ __global__ __launch_bounds__(256) void dh_reduce_kernel(const float* part, u16* 
 // the vocabulary when the output alone would leave CUs idle; `part` is the
 // fp32 partial area of the workspace (g_and_part_bytes).
 static hipError_t launch_dh(LmArgs b, float* part, const char* name, hipStream_t stream) {
-  const int nk_total = (b.V + BKK - 1) / BKK;   // G is zero past V
+  // G is written (zero from V on) up to a multiple of the tile height, 128 or
+  // 256: readers take no column past the last slice that holds one below V
+  const int nk_total = (b.V + BKK - 1) / BKK;
   int splits = dh_splits(b.T, b.H, b.V);
   b.nk_split = (nk_total + splits - 1) / splits;
   splits = (nk_total + b.nk_split - 1) / b.nk_split;  // no empty split
@@ -1154,9 +1157,10 @@ hipError_t launch_logprob_fwd(int T, int H, int V, float eps_lo, float eps_hi, c
   return logprob_fwd_common(a, ws, o, false, nullptr, stream);
 }
 
-// The forward with the GRPO loss fused into its combine pass: count the loss
-// tokens (mask given), the logits GEMM, the combine with the per-token loss
-// terms and gradient, one block for the statistics and advantages.
+// The forward with the GRPO loss fused into its combine pass: the logits GEMM
+// (which clears the status block, so it comes first), the advantages and the
+// count of the loss tokens (mask given; a word of that block), the combine with
+// the per-token loss terms and gradient, one block for the statistics.
 hipError_t launch_logprob_grpo(int T, int H, int V, float eps_lo, float eps_hi,
                                const void* hidden, const void* weight, const int32_t* target,
                                const float* logp_old, int n_traj, int G, float g_eps_lo,

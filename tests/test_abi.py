@@ -89,7 +89,7 @@ def test_backward_workspace_errors():
 def test_noalloc_backward_scratch_limit():
     """mv_attn_bwd_noalloc refuses, before anything is enqueued, a backward
     whose workspace exceeds its static scratch (the 4 x 32K batch needs
-    ~840 MiB); the 8K trajectory's (~37.5 MiB) fits and gets as far as the
+    ~854 MiB); the 8K trajectory's (56 MiB) fits and gets as far as the
     upload check."""
     big = mv.ViewMask(synth.make_trajectories("b4x32k", 0))
     sh = _shape(T=big.total_tokens, hq=28, hkv=4, d=128)
