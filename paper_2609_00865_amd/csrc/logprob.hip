@@ -31,10 +31,10 @@
 // matrix pipe is not waiting behind LDS reads, and quarter by quarter the
 // slice's LDS regions are free for the slice after next (a load has 1.5
 // slices to land).  Bound by the matrix pipe at the clock the chip holds
-// under it: at 32768 tokens x 3584 x 152064 the pipe is busy 81% (logits),
-// 73% (G) and 93% (dH) of the cycles at 1.80, 1.87 and 1.64 GHz, where the
-// earlier loop (both waves reading, then both in MFMAs; one barrier per slice)
-// had 56-64%.  Both timed in turn: at 4001 tokens logits 3.54 -> 3.22 ms, G 3.73 ->
+// under it: at 32768 tokens x 3584 x 152064, on two boxes, the pipe is busy
+// 81-82% (logits), 73-75% (G) and 93% (dH) of the cycles at 1.76-1.81,
+// 1.78-1.87 and 1.59-1.64 GHz, where the earlier loop (both waves reading, then
+// both in MFMAs; one barrier per slice) had 56-64%.  Both timed in turn: at 4001 tokens logits 3.54 -> 3.22 ms, G 3.73 ->
 // 3.20, dH 3.50 -> 3.11; at 32768: 26.7 -> 24.5, 28.6 -> 26.0, 26.0 -> 23.1.  An
 // operand slice sits in LDS as [256 rows][64] bf16 without padding, with
 // 16-byte chunk c of row r at chunk position c ^ (r & 7): the fragment reads
