@@ -4,8 +4,6 @@ import ctypes
 import os
 import subprocess
 
-import pytest
-
 from paper_2609_00865_amd import build, mv, synth
 
 HERE = os.path.dirname(os.path.abspath(__file__))
